@@ -54,7 +54,10 @@ __device__ __forceinline__ uint32_t dpp_full(uint32_t v) {
   return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xF, 0xF, false));
 }
 // per-lane predicate from a compile-time lane mask (an SGPR constant used as
-// the select mask, no per-lane arithmetic)
+// the select mask, no per-lane arithmetic).  Not for a mask whose upper half
+// is all ones over a negative lower half: the compiler may load it as a
+// sign-extended 32-bit literal, which s_mov_b64 zero-extends (use
+// lane_in_here, which loads the halves apart).
 __device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 // the same, with the constant materialised where it is used: loops with many
 // such masks would otherwise keep them all live in SGPRs across the loop
@@ -126,7 +129,7 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
   const int r0 = __builtin_amdgcn_readlane(v, 15);
   const int r1 = __builtin_amdgcn_readlane(v, 31);
   const int r2 = __builtin_amdgcn_readlane(v, 47);
-  v += lane_in(kLanesGe16) ? r0 : 0;
+  v += lane_in_here<kLanesGe16>() ? r0 : 0;
   v += lane_in(kLanesBit5) ? r1 : 0;
   v += lane_in(kLanesGe48) ? r2 : 0;
   return v;
