@@ -75,93 +75,6 @@ constexpr int kTileUnroll = 8;
 // LM target state in a cached row entry (the states are numbered below 2^23)
 constexpr uint32_t kTargetMask = (1u << 23) - 1u;
 
-// ---- fp32 log-sum-exp of the log-sum-exp recombination variant ----
-// Every step is one IEEE fp32 operation in a fixed order (no contraction), so
-// the result is reproducible bit for bit.  exp(d), -80 <= d <= 0: Cody-Waite
-// reduction d = k ln2 + r with k = rint(d / ln2) and ln2 split into a 9-bit
-// head (k * head is exact) and a tail, the degree-7 Taylor polynomial of e^r
-// by Horner, times 2^k built from its exponent bits.
-__device__ __forceinline__ float exp32_nonpos(float d) {
-  const float k = __builtin_rintf(d * 1.44269504f);
-  const float r = (d - k * 0.693359375f) - k * -2.12194440e-4f;
-  float q = 1.0f / 5040.0f;
-  q = q * r + 1.0f / 720.0f;
-  q = q * r + 1.0f / 120.0f;
-  q = q * r + 1.0f / 24.0f;
-  q = q * r + 1.0f / 6.0f;
-  q = q * r + 0.5f;
-  q = q * r + 1.0f;
-  q = q * r + 1.0f;
-  return q * __uint_as_float(static_cast<uint32_t>(static_cast<int>(k) + 127) << 23);
-}
-// log(1 + e), 2^-24 <= e <= 1: 2 atanh(s) with s = e / (2 + e) <= 1/3, the odd
-// series to s^17 by Horner in s^2.
-__device__ __forceinline__ float log1p32_unit(float e) {
-  const float s = e / (2.0f + e);
-  const float z = s * s;
-  float q = 1.0f / 17.0f;
-  q = q * z + 1.0f / 15.0f;
-  q = q * z + 1.0f / 13.0f;
-  q = q * z + 1.0f / 11.0f;
-  q = q * z + 1.0f / 9.0f;
-  q = q * z + 1.0f / 7.0f;
-  q = q * z + 1.0f / 5.0f;
-  q = q * z + 1.0f / 3.0f;
-  q = q * z + 1.0f;
-  const float t = s * q;
-  return t + t;
-}
-// log(exp(a) + exp(b))
-__device__ __forceinline__ float lse32(float a, float b) {
-  const float hi = (a < b) ? b : a;
-  const float lo = (a < b) ? a : b;
-  if (lo == kNegInf) return hi;
-  const float d = lo - hi;
-  if (d < -80.0f) return hi;
-  const float e = exp32_nonpos(d);
-  const float l = (e < 5.9604645e-8f) ? e : log1p32_unit(e);
-  return hi + l;
-}
-
-// Bitonic sort of (hi, lo, slot) triples, one per lane, ascending over the
-// wave (slots are distinct, so the order is total).
-template <int k, int jd>
-__device__ __forceinline__ void sort3_step(uint32_t& lo, uint32_t& hi, uint32_t& sl, int lane) {
-  const uint32_t olo = xor_lane(lo, jd, lane), ohi = xor_lane(hi, jd, lane), osl = xor_lane(sl, jd, lane);
-  const bool less = ohi < hi || (ohi == hi && (olo < lo || (olo == lo && osl < sl)));
-  // lanes that keep the larger in the descending network keep the smaller here
-  const bool take = less == lane_in_here<bitonic_max_lanes(k, jd, 64)>();
-  lo = take ? olo : lo;
-  hi = take ? ohi : hi;
-  sl = take ? osl : sl;
-}
-template <int k, int jd>
-__device__ __forceinline__ void sort3_merge(uint32_t& lo, uint32_t& hi, uint32_t& sl, int lane) {
-  sort3_step<k, jd>(lo, hi, sl, lane);
-  if constexpr (jd > 1) sort3_merge<k, jd / 2>(lo, hi, sl, lane);
-}
-template <int k>
-__device__ __forceinline__ void sort3_levels(uint32_t& lo, uint32_t& hi, uint32_t& sl, int lane) {
-  sort3_merge<k, k / 2>(lo, hi, sl, lane);
-  if constexpr (k < 64) sort3_levels<k * 2>(lo, hi, sl, lane);
-}
-// Recombination of up to 64 slots (lane = slot): sorts the 64-bit keys with
-// their slots and flags each slot whose sorted predecessor has the same key,
-// i.e. a lower slot with the same transcript.  Dead slots carry all ones and
-// are never flagged.  The sorted keys are left in lo / hi (for searches).
-__device__ __forceinline__ bool dup_by_sort(uint64_t key, int lane, uint32_t& lo, uint32_t& hi) {
-  lo = static_cast<uint32_t>(key);
-  hi = static_cast<uint32_t>(key >> 32);
-  uint32_t sl = static_cast<uint32_t>(lane);
-  sort3_levels<2>(lo, hi, sl, lane);
-  const int pa = (lane == 0 ? 63 : lane - 1) << 2;
-  const uint32_t plo = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(pa, static_cast<int>(lo)));
-  const uint32_t phi = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(pa, static_cast<int>(hi)));
-  const bool d = lane > 0 && plo == lo && phi == hi && (lo & hi) != 0xFFFFFFFFu;
-  // back to the slot's lane (the slots are a permutation of the lanes)
-  return __builtin_amdgcn_ds_permute(static_cast<int>(sl) << 2, d ? 1 : 0) != 0;
-}
-
 // Per-phase clocks (profiling builds, -DCTCBEAM_PHASE_CLOCKS; the macro is in
 // ctcbeam_internal.h): each wave adds the s_memtime cycles of every phase of
 // every frame (fill, barrier A, candidates, barrier B, filter, barrier C,
@@ -170,28 +83,24 @@ __device__ __forceinline__ bool dup_by_sort(uint64_t key, int lane, uint32_t& lo
 // chunk plan; then the bound, split from the filter) and writes them after the [B, 8] statistics as
 // [B, kWaves, kPhaseWords] int64.
 
-// SPL = beam slots per lane: slot j lives in lane j % 64, register set
-// j / 64 (SPL = 2 serves beams of 65..128).  SKIP: ranks of chunks before
-// the last are skipped while the survivor pool has room (beams above one
-// chunk; small beams keep one rank per chunk and the simpler code).
-// CACHE (one chunk, one slot per lane, LM without boosting, LM states below
-// 2^23): LM key rows are kept per LM state across frames and only the states
-// new to the rows are filled; an entry holds its arc's target state.
+// SKIP: ranks of chunks before the last are skipped while the survivor pool
+// has room (beams above one chunk; beams of one chunk keep the simpler code).
+// CACHE (one chunk, LM without boosting, LM states below 2^23): LM key rows
+// are kept per LM state across frames and only the states new to the rows are
+// filled; an entry holds its arc's target state.
 // REP: the repeat-scoring variant (CTCBEAM_FLAG_REPEAT_SCORE), a kernel of
-// its own so that the default kernels carry none of its state.  TREE (beams
-// of 33..64): pools of more than 192 entries are reduced to their top 64 by
-// a merge tree instead of the block rank (a kernel of its own: the code
-// costs the smaller beams' kernels about 3 % through register allocation).
-template <int LPT, int NLEV, bool HAS_BT, int SPL, bool SKIP, bool CACHE, bool REP, bool TREE>
+// its own so that the default kernels carry none of its state.
+// Serves beams of one chunk (at most 16 / LPT) and, above 2048 tokens with an
+// LM, of at most 16; the class decoder serves the rest.
+template <int LPT, int NLEV, bool HAS_BT, bool SKIP, bool CACHE, bool REP>
 __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
+  constexpr int SPL = 1;                      // beam slots per lane
   constexpr bool HAS_LM = NLEV >= 0;
   constexpr int NL = NLEV > 0 ? NLEV : 0;     // chain levels above the unigram root
   constexpr int NLA = NL > 0 ? NL : 1;        // array extent
   constexpr int NF = NL > 1 ? NL - 1 : 1;     // backoff weights folded into an arc (extent)
   constexpr int KMX = 64 * SPL;               // slot capacity
-  // beams (key rows) per chunk; two slots per lane leave LDS for 12 rows of
-  // 1024 labels instead of 16
-  constexpr int KCR = (SPL == 1 ? 16 : 12) / LPT;
+  constexpr int KCR = 16 / LPT;               // beams (key rows) per chunk
   // LDS scratch carved from one block so the traceback can reuse it:
   // [LM rows: KW x u64][boosting rows: KW x u32][LM targets: kLmStage]
   constexpr int KW = KCR * LPT * kThreads;
@@ -203,7 +112,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   constexpr int KSEG = (NL > 0 && KCR * NL > 64) ? 64 / (NL > 0 ? NL : 1) : KCR;
   // without rank skipping the beam fits one chunk of 16 / LPT rows: K <= 8
   // for two or more labels per lane
-  constexpr bool kSmallK = SPL == 1 && !SKIP && LPT >= 2;
+  constexpr bool kSmallK = !SKIP && LPT >= 2;
   // rank skipping means K > 16 / LPT: no beam of at most 8 for LPT <= 2
   constexpr bool kMaySmallK = !SKIP || LPT > 2;
   // LM arc tiles in flight per wave: cached rows fill only the new states
@@ -217,7 +126,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   // one slot per lane, whose backoff weights would otherwise take KCR x NL
   // registers in the scoring.  Shorter chains, and the many chunks of two
   // slots per lane, fold in the scoring: cheaper than the extra LDS maxima.
-  constexpr bool kFoldRows = CACHE || (NL >= 4 && SPL == 1);
+  constexpr bool kFoldRows = CACHE || NL >= 4;
   // Fill groups (beams over one chunk, no row cache): the update orders the
   // live beams by LM state and cuts that order into groups of consecutive
   // chunks whose distinct LM states (at most KSEG), boosting lists (at most
@@ -263,12 +172,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   __shared__ float s_top[kWaves * 8 * SPL + kWaves];
   __shared__ uint64_t s_red[2][kWaves];
   __shared__ int32_t s_nbuf, s_overflow;
-  // top 64 of a large pool (one slot per lane, beams over one chunk): the
-  // sorted lists of the merge tree (4 + 2 + 1 lists of 64 (lo, hi, source)
-  // triples) and the waves' counts of finite entries
-  constexpr bool kTreeRank = SPL == 1 && SKIP && TREE;
-  __shared__ uint32_t s_srt[kTreeRank ? 7 : 1][3][64];
-  __shared__ int32_t s_wcnt[kWaves];
   __shared__ int32_t s_best, s_bestlen;
   __shared__ float s_bestscore;
   // statistics (only with p.stats): alive beam-frames, LM chain states and
@@ -797,7 +700,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
     }
     float tau_run = kNegInf;
     float gacc = kNegInf;  // top 64 group maxima of the frame's chunks so far (K > 8)
-    float gacc_hi = kNegInf;  // two slots per lane: positions 64..127 of the top 128
     int nfin = 0;
     // survivors carried in the pool from chunks whose rank was skipped
     int carry = 0;
@@ -809,20 +711,10 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       bool inch[SPL];
       int row[SPL];
       int kc = 0;
-      if constexpr (SPL == 1) {
-        inch[0] = alive[0] && (cid[0] == ch);
-        const uint64_t chmask = __ballot(inch[0]);
-        kc = __popcll(chmask);
-        row[0] = __popcll(chmask & lmlt);
-      } else {
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) {
-          inch[h] = alive[h] && (cid[h] == ch);
-          const uint64_t chmask = __ballot(inch[h]);
-          row[h] = kc + __popcll(chmask & lmlt);
-          kc += __popcll(chmask);
-        }
-      }
+      inch[0] = alive[0] && (cid[0] == ch);
+      const uint64_t chmask = __ballot(inch[0]);
+      kc = __popcll(chmask);
+      row[0] = __popcll(chmask & lmlt);
 
       // ---- F. fill the key rows of this chunk (of its group) ----
       // kGroups: only a group's first chunk fills (uniform)
@@ -1310,23 +1202,12 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
           bk = (be >= genhi) ? be : rRoot[jj];
         }
       };
-      if (SPL == 1 && ch == 0 && wave == 0 && lane < K) {
+      if (ch == 0 && wave == 0 && lane < K) {
         // blank candidates of every slot into the reserved region
         const float x = sc[0] + rBlank;
         const bool ok = sc[0] != kNegInf && x != kNegInf;
         s_res[mpar][j] = make_uint4(__float_as_uint(ok ? x : kNegInf),
                                     ok ? static_cast<uint32_t>(j * W + V) : 0xFFFFFFFFu, 0u, 0u);
-      } else if (SPL > 1 && ch == 0 && wave == 0) {
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) {
-          const int js = j + 64 * h;
-          if (js < K) {
-            const float x = sc[h] + rBlank;
-            const bool ok = sc[h] != kNegInf && x != kNegInf;
-            s_res[mpar][js] = make_uint4(__float_as_uint(ok ? x : kNegInf),
-                                         ok ? static_cast<uint32_t>(js * W + V) : 0xFFFFFFFFu, 0u, 0u);
-          }
-        }
       }
       if (tid == 0 && carry == 0) {
         s_nbuf = 0;  // the previous rank read it before barrier D
@@ -1338,11 +1219,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       // for K <= 8 also (row, half of the waves) and the waves; the groups of
       // earlier chunks of the frame still count.  Two slots per lane: 128
       // groups of 4 lanes.
-      if (SPL > 1) {
-        float g = fmax_sel(lmax, xor_lane(lmax, 1, lane));
-        g = fmax_sel(g, xor_lane(g, 2, lane));
-        if ((lane & 3) == 3) s_top[wave * 16 + (lane >> 2)] = g;
-      } else {
+      {
         // The wave maxima of 8 row groups (row i, and i + 8 when a chunk has
         // 16 rows): a transposed reduction halves the groups a lane carries
         // at each of the lane-bit steps 1, 2, 4, leaving lane l with group
@@ -1387,8 +1264,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
         tb = fmin_sel(tb, xor_lane(tb, 2, lane));
         tb = fmin_sel(tb, xor_lane(tb, 4, lane));
         if (K > 8) tb = fmin_sel(tb, xor_lane(tb, 8, lane));
-        if (K > 16) tb = fmin_sel(tb, xor_lane(tb, 16, lane));
-        if (K > 32) tb = fmin_sel(tb, xor_lane(tb, 32, lane));
         return rdlane(tb, 0);
       };
       float tblank = 0.0f;
@@ -1419,7 +1294,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
           // least K values of its row at or above it
           const float kv = row_max_last(row_ge_count(v) >= static_cast<uint32_t>(K) ? v : kNegInf);
           tc = fmaxf(rdlane(kv, 15), rdlane(kv, 31));
-        } else if (SPL == 1) {
+        } else {
           // this chunk's 64 (row group, wave) maxima, sorted ascending, merged
           // into the frame's running top 64 (descending): the elementwise
           // maximum of the two is bitonic and holds the top 64 of the union
@@ -1432,23 +1307,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
             gacc = bitonic_merge<64, 64, 32>(fmaxf(SKIP ? gacc : kNegInf, v), lane);
           }
           tc = rdlane(gacc, K - 1);
-        } else {
-          // This chunk's 128 group maxima, sorted ascending, merged into the
-          // frame's running top 128 (descending; positions 0..63 in gacc, 64..127
-          // in gacc_hi), as for one slot per lane.  The ascending sort runs on
-          // the negated values: the halves sorted descending and ascending
-          // form a bitonic sequence, merged descending by one exchange
-          // between the halves and a 64-lane merge in each.
-          const float e0 = wave_sort_desc<64>(-s_top[lane], lane);
-          const float f1 = -wave_sort_desc<64>(s_top[64 + lane], lane);
-          const float n0 = -bitonic_merge<64, 64, 32>(fmaxf(e0, f1), lane);
-          const float n1 = -bitonic_merge<64, 64, 32>(fminf(e0, f1), lane);
-          // the elementwise maximum with the descending top 128 is bitonic and
-          // holds the top 128 of the union
-          const float m0 = fmaxf(gacc, n0), m1 = fmaxf(gacc_hi, n1);
-          gacc = bitonic_merge<64, 64, 32>(fmaxf(m0, m1), lane);
-          gacc_hi = bitonic_merge<64, 64, 32>(fminf(m0, m1), lane);
-          tc = K <= 64 ? rdlane(gacc, K - 1) : rdlane(gacc_hi, K - 65);
         }
         if constexpr (!kSmallK) tblank = blank_bound();
         // an infinite bound admits every finite candidate and no -inf one
@@ -1524,7 +1382,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       // chunk (with large beams most chunks skip it).
       const bool last_chunk = ch + 1 == nch;
       const int npool = s_nbuf;
-      if (SKIP && !last_chunk && !s_overflow && npool <= (SPL > 1 ? kCap / 4 : kCap / 2)) {  // uniform
+      if (SKIP && !last_chunk && !s_overflow && npool <= kCap / 2) {  // uniform
         carry = npool;
         cs += kc;
         CTCBEAM_PHASE_COUNT(10);  // chunks
@@ -1569,74 +1427,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
             } else if (own && myrank < K) {
               s_res[Q][myrank] = make_uint4(eq.x, eq.y, lmt, eq.w);
               if (rep) s_rinc[Q][myrank] = (lane < K) ? s_rinc[P][lane] : s_pinc[lane - K];
-            }
-          } else if (kTreeRank && N > 192 && N <= kThreads) {
-            CTCBEAM_PHASE_COUNT(16);  // merge-tree ranks
-            // K <= 64 of 193..512 entries (a few blocks of 64 are cheaper to
-            // rank against each other): each wave sorts its 64 entries by
-            // (score desc, index asc) as 64-bit keys, then a tree of pairwise
-            // merges keeps the top 64 (the 64 largest of two ascending lists
-            // are the elementwise maximum of one and the other reversed, a
-            // bitonic sequence), instead of ranking every entry against
-            // every other
-            const int q = tid;
-            uint4 eq = make_uint4(__float_as_uint(kNegInf), 0xFFFFFFFFu, 0u, 0u);
-            if (q < N) eq = (q < K) ? s_res[P][q] : s_pool[q - K];
-            const float xq = __uint_as_float(eq.x);
-            const uint64_t key = xq != kNegInf ? order_key(xq, eq.y) : 0ull;
-            uint32_t klo = static_cast<uint32_t>(key), khi = static_cast<uint32_t>(key >> 32);
-            uint32_t ksl = static_cast<uint32_t>(q);
-            sort3_levels<2>(klo, khi, ksl, lane);  // ascending over the wave
-            const int wcnt = __popcll(__ballot(xq != kNegInf));
-            if (lane == 0) s_wcnt[wave] = wcnt;
-            const auto publish = [&](int r) __attribute__((always_inline)) {
-              s_srt[r][0][lane] = klo;
-              s_srt[r][1][lane] = khi;
-              s_srt[r][2][lane] = ksl;
-            };
-            const auto merge_with = [&](int r) __attribute__((always_inline)) {
-              const uint32_t olo = s_srt[r][0][63 - lane], ohi = s_srt[r][1][63 - lane];
-              const uint32_t osl = s_srt[r][2][63 - lane];
-              const bool gt = ohi > khi || (ohi == khi && (olo > klo || (olo == klo && osl > ksl)));
-              klo = gt ? olo : klo;
-              khi = gt ? ohi : khi;
-              ksl = gt ? osl : ksl;
-              sort3_merge<64, 32>(klo, khi, ksl, lane);
-            };
-            if (wave & 1) publish(wave >> 1);  // waves 1, 3, 5, 7: lists 0..3
-            __syncthreads();
-            nfin = 0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) nfin += s_wcnt[w];
-            if ((wave & 1) == 0) merge_with(wave >> 1);
-            if ((wave & 3) == 2) publish(4 + (wave >> 2));  // waves 2, 6: lists 4, 5
-            __syncthreads();
-            if ((wave & 3) == 0) merge_with(4 + (wave >> 2));
-            if (wave == 4) publish(6);
-            __syncthreads();
-            if (wave == 0) {
-              merge_with(6);
-              // lane 63 holds the best entry: rank 63 - lane
-              const int rank = 63 - lane;
-              if (rank < min(K, nfin)) {
-                const uint32_t qq = ksl;
-                const uint4 e = (qq < static_cast<uint32_t>(K)) ? s_res[P][qq] : s_pool[qq - K];
-                uint32_t lmt = e.z;
-                if (HAS_LM && !SKIP && !CACHE && qq >= static_cast<uint32_t>(K)) lmt = lm_target(lmt);
-                s_res[Q][rank] = make_uint4(e.x, e.y, lmt, e.w);
-                if (rep) s_rinc[Q][rank] = (qq < static_cast<uint32_t>(K)) ? s_rinc[P][qq] : s_pinc[qq - K];
-              }
-            }
-            if (last_chunk) {
-              __syncthreads();  // region Q complete
-              const bool act = wave == 0 && tid < min(K, nfin);
-              uint4 e = make_uint4(__float_as_uint(kNegInf), 0xFFFFFFFFu, 0u, 0u);
-              if (act) e = s_res[Q][tid];
-              Succ sp;
-              succ_begin(act, e.y, e.z, e.w, prec, sp);
-              succ_end(sp, e.x);
-              if (act) store_rec(nrec + tid * RW, sp.r);
-              if (rep && act && sp.emit) put_terms(nrec + tid * RW, s_rinc[Q][tid]);
             }
           } else {
             // blocks of 64 entries: this wave ranks entries qb + (wave + 8u)
@@ -1687,7 +1477,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
               __syncthreads();  // region Q complete
               // rank tid (waves 0 .. SPL-1): the chain-header loads of all
               // winners are in flight together
-              const bool act = (SPL > 1 || wave == 0) && tid < min(K, nfin);
+              const bool act = wave == 0 && tid < min(K, nfin);
               uint4 e = make_uint4(__float_as_uint(kNegInf), 0xFFFFFFFFu, 0u, 0u);
               if (act) e = s_res[Q][tid];
               Succ sp;
@@ -1809,7 +1599,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
           if (last_chunk) {
             __syncthreads();  // region Q complete
             // rank tid (waves 0 .. SPL-1)
-            const bool act = (SPL > 1 || wave == 0) && tid < nk;
+            const bool act = wave == 0 && tid < nk;
             uint4 e = make_uint4(__float_as_uint(kNegInf), 0xFFFFFFFFu, 0u, 0u);
             if (act) e = s_res[Q][tid];
             Succ sp;
@@ -1820,7 +1610,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
           }
         }
         // ranks [nfin, K) hold no candidate (the next chunk reads all K)
-        if (!last_chunk && (SPL > 1 || wave == 0) && tid >= nfin && tid < K)
+        if (!last_chunk && wave == 0 && tid >= nfin && tid < K)
           s_res[Q][tid] = make_uint4(__float_as_uint(kNegInf), 0xFFFFFFFFu, 0u, 0u);
       }
       CTCBEAM_PHASE_MARK(6);
@@ -1833,10 +1623,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       cs += kc;
     }
 
-    // The single-slot form (K <= 64) is kept apart from the general one: the
-    // general form, instantiated with one slot per lane, changes the register
-    // allocation of the frame loop and costs about 2 % at K = 8.
-    if constexpr (SPL == 1) {
     // ---- U. prune, recombine, take the new beam (every wave, lane j = slot j) ----
     {
       const int nsel = min(K, nfin);
@@ -1859,7 +1645,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       const bool alive0 = valid && x != kNegInf;
       const uint32_t meta = (static_cast<uint32_t>(nlen) & 0x3FFFFFFFu) | ((nlast == V ? 1u : 0u) << 30);
       bool dup = false;
-      if (K <= 16) {
+      {
         // The K slots sit in the first 16-lane row: compare each with the
         // slots below it through row shifts.  The key folds the length and
         // the ends-in-blank flag into the 64-bit transcript hash (a false
@@ -1870,13 +1656,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
         if (!alive0) key = ~0ull;
         const uint32_t klo = static_cast<uint32_t>(key), khi = static_cast<uint32_t>(key >> 32);
         dup = (K <= 8 ? recomb_shifts<1, 7>(klo, khi) : recomb_shifts<1, 15>(klo, khi)) && alive0;
-      } else {
-        // the same key, compared through a sort of all 64 slots
-        uint64_t key = ((static_cast<uint64_t>(rec[kRHhi]) << 32) | rec[kRHlo]) ^
-                       (static_cast<uint64_t>(meta + 1u) * 0xD6E8FEB86659FD93ull);
-        if (!alive0) key = ~0ull;
-        uint32_t slo, shi;
-        dup = dup_by_sort(key, lane, slo, shi) && alive0;
       }
       if (p.flags & kFlagLogSumExp) {  // uniform
         // Each duplicate, in slot order, is merged into the first live slot
@@ -2049,226 +1828,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       }
       }
     }
-    } else {
-    // ---- U. prune, recombine, take the new beam (every wave; slot
-    // j + 64 h in register set h) ----
-    {
-      const int nsel = min(K, nfin);
-      uint32_t rec[SPL][RW];
-      float x[SPL];
-      bool valid[SPL], alive0[SPL], dup[SPL], emit_fin[SPL];
-      int32_t nlast[SPL], nlen[SPL];
-      uint32_t meta[SPL];
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        valid[h] = j + 64 * h < nsel;
-#pragma unroll
-        for (int w = 0; w < RW; ++w) rec[h][w] = 0u;
-        if (valid[h]) load_rec(s_rec + (rcur ^ 1) * (KMX * RW) + (j + 64 * h) * RW, rec[h]);
-        x[h] = valid[h] ? __uint_as_float(rec[h][kRX]) : kNegInf;
-      }
-      // prune (Algorithm 1: below best - theta -> -inf)
-      const float best = rdlane(x[0], 0);
-      const float lim = best - p.theta;
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        if (valid[h] && x[h] < lim) x[h] = kNegInf;
-        const bool emit = valid[h] && rec[h][kREmit] != 0u;
-        emit_fin[h] = x[h] != kNegInf && emit;
-        nlast[h] = valid[h] ? static_cast<int32_t>(rec[h][kRLast]) : V;
-        nlen[h] = static_cast<int32_t>(rec[h][kRLen]);
-        // recombination key: transcript hash, length and ends-in-blank flag
-        alive0[h] = valid[h] && x[h] != kNegInf;
-        meta[h] = (static_cast<uint32_t>(nlen[h]) & 0x3FFFFFFFu) | ((nlast[h] == V ? 1u : 0u) << 30);
-        dup[h] = false;
-      }
-      if (K <= 16) {
-        // The K slots sit in the first 16-lane row: compare each with the
-        // slots below it through row shifts.  The key folds the length and
-        // the ends-in-blank flag into the 64-bit transcript hash (a false
-        // merge needs a 64-bit collision, as for the hash itself); dead
-        // slots use all ones and are never merged into.
-        uint64_t key = ((static_cast<uint64_t>(rec[0][kRHhi]) << 32) | rec[0][kRHlo]) ^
-                       (static_cast<uint64_t>(meta[0] + 1u) * 0xD6E8FEB86659FD93ull);
-        if (!alive0[0]) key = ~0ull;
-        const uint32_t klo = static_cast<uint32_t>(key), khi = static_cast<uint32_t>(key >> 32);
-        dup[0] = (K <= 8 ? recomb_shifts<1, 7>(klo, khi) : recomb_shifts<1, 15>(klo, khi)) && alive0[0];
-      } else {
-        // Each register set is sorted on its own (its slots are in lane
-        // order); a slot of the upper set is also a duplicate when its key
-        // occurs among the live keys of the lower set (all lower slots):
-        // binary search in the lower set's sorted keys.
-        uint64_t key[SPL];
-        uint32_t slo[SPL], shi[SPL];
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) {
-          key[h] = ((static_cast<uint64_t>(rec[h][kRHhi]) << 32) | rec[h][kRHlo]) ^
-                   (static_cast<uint64_t>(meta[h] + 1u) * 0xD6E8FEB86659FD93ull);
-          if (!alive0[h]) key[h] = ~0ull;
-          dup[h] = dup_by_sort(key[h], lane, slo[h], shi[h]) && alive0[h];
-        }
-#pragma unroll
-        for (int h = 1; h < SPL; ++h) {
-          // position of the first lower key >= key[h]
-          int pos = 0;
-          const uint64_t kh = key[h];
-#pragma unroll
-          for (int step = 32; step >= 1; step >>= 1) {
-            const int a = (pos + step - 1) << 2;
-            const uint64_t v = (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(a, static_cast<int>(shi[0])))) << 32) |
-                               static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(a, static_cast<int>(slo[0])));
-            pos += (v < kh) ? step : 0;
-          }
-          // pos <= 63: the last lower key decides the 64th position
-          const uint64_t at = (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(pos << 2, static_cast<int>(shi[0])))) << 32) |
-                              static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(pos << 2, static_cast<int>(slo[0])));
-          dup[h] = dup[h] || (alive0[h] && at == kh);
-        }
-      }
-      if (p.flags & kFlagLogSumExp) {  // uniform
-        // Each duplicate, in slot order, is merged into the first live slot
-        // of its transcript (a lower slot, which is not a duplicate itself).
-        float xs[SPL];
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) xs[h] = x[h];
-#pragma unroll
-        for (int hj = 0; hj < SPL; ++hj) {
-          uint64_t dm = __ballot(dup[hj]);
-          while (dm) {
-            const int jj = static_cast<int>(__builtin_ctzll(dm));
-            dm &= dm - 1ull;
-            const uint32_t hlo = rdlane(rec[hj][kRHlo], jj);
-            const uint32_t hhi = rdlane(rec[hj][kRHhi], jj);
-            const uint32_t mj = rdlane(meta[hj], jj);
-            int rep = -1;  // the duplicate itself matches, so some slot does
-#pragma unroll
-            for (int h = SPL - 1; h >= 0; --h) {
-              const uint64_t same =
-                  __ballot(alive0[h] && rec[h][kRHlo] == hlo && rec[h][kRHhi] == hhi && meta[h] == mj);
-              if (same) rep = static_cast<int>(__builtin_ctzll(same)) + 64 * h;
-            }
-            const float xj = rdlane(xs[hj], jj);
-#pragma unroll
-            for (int h = 0; h < SPL; ++h)
-              if (j + 64 * h == rep && rep != jj + 64 * hj) x[h] = lse32(x[h], xj);
-          }
-        }
-      }
-      bool nalive[SPL];
-      int32_t acnt[SPL];
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        if (dup[h]) x[h] = kNegInf;
-        nalive[h] = alive0[h] && !dup[h];
-        const int js = j + 64 * h;
-        if (wave == 1 && js < K)
-          bpb[static_cast<size_t>(t) * K + js] = valid[h] ? static_cast<int32_t>(rec[h][kRBp]) : -1;
-        // new state
-        sc[h] = x[h];
-        last[h] = nlast[h];
-        len[h] = nlen[h];
-        alive[h] = nalive[h];
-        acnt[h] = 0;
-#pragma unroll
-        for (int l = 0; l < NL; ++l) {
-          lvb[h][l] = nalive[h] ? rec[h][kRLvb + l] : 0u;
-          lvc[h][l] = nalive[h] ? rec[h][kRLvc + l] : 0u;
-          lvbo[h][l] = nalive[h] ? __uint_as_float(rec[h][kRLvbo + l]) : 0.0f;
-          acnt[h] += static_cast<int32_t>(lvc[h][l] & ~kExists);
-        }
-        if (HAS_BT) {
-          btb[h] = nalive[h] ? rec[h][kRBtb] : 0u;
-          btc[h] = nalive[h] ? rec[h][kRBtc] : 0u;
-          btpot[h] = nalive[h] ? static_cast<int32_t>(rec[h][kRBtp]) : 0;
-        }
-        if (want_stats && wave == 0) {
-          // chain work of the next frame (alive beams) and this frame's
-          // emitting winners
-          uint32_t s_ls = 0u, s_la = 0u, s_bn = 0u, s_ba = 0u;
-          const bool counted = t + 1 < L && nalive[h];
-          if (counted) {
-#pragma unroll
-            for (int l = 0; l < NL; ++l) {
-              if (lvc[h][l] & kExists) {
-                s_ls += 1u;
-                s_la += lvc[h][l] & ~kExists;
-              }
-            }
-            if (HAS_BT) {
-              const BtNode pn = p.bt_nodes[rec[h][kRBts]];
-              s_bn = pn.pot >> 8;
-              s_ba = pn.chain_arcs;
-            }
-            atomicAdd(&s_st[0], 1ull);
-          }
-          if (s_ls) atomicAdd(&s_st[1], static_cast<unsigned long long>(s_ls));
-          if (s_la) atomicAdd(&s_st[2], static_cast<unsigned long long>(s_la));
-          if (s_bn) atomicAdd(&s_st[3], static_cast<unsigned long long>(s_bn));
-          if (s_ba) atomicAdd(&s_st[4], static_cast<unsigned long long>(s_ba));
-          if (emit_fin[h]) atomicAdd(&s_st[5], 1ull);
-        }
-      }
-      rcur ^= 1;
-      // live positions (slot order) and beam records for the next frame;
-      // ia = inclusive scan of the staged arcs over the slots
-      int lp[SPL], ia[SPL];
-      int na = 0, tota = 0;
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        const uint64_t amask = __ballot(nalive[h]);
-        lp[h] = na + __popcll(amask & lmlt);
-        na += __popcll(amask);
-        if (!kGroups && wave == 2 && nalive[h]) put_row(lp[h], h);
-        ia[h] = tota + wave_incl_scan(acnt[h], lane);
-        tota = rdlane(ia[h], 63);
-      }
-      if constexpr (kGroups) {
-        uint32_t lk[SPL];
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) lk[h] = (HAS_LM && NL > 0 && nalive[h]) ? rec[h][kRLms] : 0u;
-        plan_groups(nalive, acnt, lk, lp);
-#pragma unroll
-        for (int h = 0; h < SPL; ++h)
-          if (wave == 2 && nalive[h]) put_row(lp[h], h);
-      } else if (na <= kcmax && tota <= kLmStage) {
-        // chunk plan: live slots in slot order, at most kcmax beams and
-        // kLmStage staged arcs per chunk
-        nch = na > 0 ? 1 : 0;
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) cid[h] = 0;
-      } else {
-        nch = 0;
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) cid[h] = -1;
-        int start = 0;
-        while (start < na) {
-          // staged arcs before the chunk's first beam (the slot at live
-          // position start)
-          int basea = 0;
-#pragma unroll
-          for (int h = SPL - 1; h >= 0; --h) {
-            const uint64_t sm = __ballot(nalive[h] && lp[h] == start);
-            if (sm) basea = rdlane(ia[h] - acnt[h], static_cast<int>(__builtin_ctzll(sm)));
-          }
-          int cnt = 0;
-#pragma unroll
-          for (int h = 0; h < SPL; ++h) {
-            const bool ok = nalive[h] && lp[h] >= start && lp[h] < start + kcmax && (ia[h] - basea) <= kLmStage;
-            cnt += __popcll(__ballot(ok));
-          }
-          if (cnt == 0) {
-            cnt = 1;  // a single chain above the staging limit (the builders prevent it)
-            status |= 4u;
-          }
-#pragma unroll
-          for (int h = 0; h < SPL; ++h)
-            if (nalive[h] && lp[h] >= start && lp[h] < start + cnt) cid[h] = nch;
-          ++nch;
-          start += cnt;
-        }
-      }
-    }
-    }
     CTCBEAM_PHASE_MARK(8);
     CTCBEAM_PHASE_COUNT(9);  // frames
   }
@@ -2279,8 +1838,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   }
 #endif
 
-  // single-slot and general forms kept apart, as for the beam update
-  if constexpr (SPL == 1) {
   // ---- LM.Final, order of the final hypotheses ----
   const bool nbest = p.nbest_scores != nullptr;
   if (wave == 0) {
@@ -2420,254 +1977,60 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
     }
     if (wave == 0 && __ballot(walker && pos != 0) != 0ull) status |= 2u;
   }
-  } else {
-  // ---- LM.Final, order of the final hypotheses ----
-  const bool nbest = p.nbest_scores != nullptr;
-  if (wave == 0) {
-    float sj[SPL];
-#pragma unroll
-    for (int h = 0; h < SPL; ++h) {
-      const int js = j + 64 * h;
-      float s = sc[h];
-      if (HAS_LM && js < K && s != kNegInf) {
-        // ln P(</s> | state) through the backoff chain; </s> is the last arc
-        // of a state's sorted arcs when present
-        float v = p.lm_unigram[V];
-        int found = -1;
-        float fv = 0.0f;
-#pragma unroll
-        for (int l = NL - 1; l >= 0; --l) {
-          const uint32_t n = lvc[h][l] & ~kExists;
-          if (found < 0 && n > 0) {
-            const LmArc a = p.lm_arcs[lvb[h][l] + n - 1];
-            if (a.token == static_cast<uint32_t>(V)) {
-              found = l;
-              fv = a.logp;
-            }
-          }
-        }
-        if (found >= 0) {
-          v = fv;
-#pragma unroll
-          for (int l = 0; l < NL; ++l)
-            if (l > found) v = v + lvbo[h][l];
-        } else {
-#pragma unroll
-          for (int l = 0; l < NL; ++l) v = v + lvbo[h][l];
-        }
-        const float av = alpha * v;
-        s = s + av;
-      }
-      if (HAS_BT && (p.flags & kFlagBoostRollback) && js < K && s != kNegInf) {
-        // the pending boosting of an unfinished phrase is taken back
-        const float wb = boost_w * static_cast<float>(-btpot[h]);
-        s = s + wb;
-      }
-      sj[h] = (js < K) ? s : kNegInf;
-    }
-    // rank of each slot: final score descending, lowest slot on ties
-    int rank[SPL];
-#pragma unroll
-    for (int h = 0; h < SPL; ++h) rank[h] = 0;
-    for (int i = 0; i < K; ++i) {
-      const float si = (i < 64) ? rdlane(sj[0], i) : rdlane(sj[SPL - 1], i & 63);
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) rank[h] += (si > sj[h] || (si == sj[h] && i < j + 64 * h)) ? 1 : 0;
-    }
-    int bj = 0;  // K >= 1: some slot has rank 0
-#pragma unroll
-    for (int h = SPL - 1; h >= 0; --h) {
-      const uint64_t top = __ballot(j + 64 * h < K && rank[h] == 0);
-      if (top) bj = static_cast<int>(__builtin_ctzll(top)) + 64 * h;
-    }
-    const float bs = (bj < 64) ? rdlane(sj[0], bj) : rdlane(sj[SPL - 1], bj & 63);
-    const int blen = (bj < 64) ? rdlane(len[0], bj) : rdlane(len[SPL - 1], bj & 63);
-#pragma unroll
-    for (int h = 0; h < SPL; ++h) {
-      const int js = j + 64 * h;
-      const int nlen = (js < K && sj[h] != kNegInf) ? len[h] : 0;
-      if (nbest && js < K) {
-        p.nbest_scores[static_cast<size_t>(b) * K + rank[h]] = sj[h];
-        p.nbest_lengths[static_cast<size_t>(b) * K + rank[h]] = nlen;
-        s_row[rank[h]] = static_cast<uint32_t>(nlen);  // lengths by rank (the row table is free now)
-        s_row[KMX + js] = static_cast<uint32_t>(rank[h]);
-      }
-    }
-    if (lane == 0) {
-      s_best = bj;
-      s_bestscore = bs;
-      s_bestlen = blen;
-    }
-    if (want_stats && lane == 0) {
-      // wave 0 made every update of s_st (LDS operations of one wave complete
-      // in order)
-      int64_t* so = p.stats + static_cast<size_t>(b) * 8;
-      so[0] = L;
-#pragma unroll
-      for (int q = 0; q < 6; ++q) so[1 + q] = static_cast<int64_t>(s_st[q]);
-      so[7] = 0;
-    }
-  }
-  __syncthreads();
-  const int best = s_best;
-  const float bscore = s_bestscore;
-  const bool have = bscore != kNegInf;
-  const int nout = have ? s_bestlen : 0;
-  int32_t* ot = p.out_tokens ? p.out_tokens + static_cast<size_t>(b) * T : nullptr;
-  if (ot)
-    for (int tt = nout + tid; tt < T; tt += kThreads) ot[tt] = -1;
-  if (tid == 0 && p.out_scores) {
-    p.out_scores[b] = bscore;
-    if (p.out_lengths) p.out_lengths[b] = nout;
-  }
-  int32_t* nbt = nbest ? p.nbest_tokens + static_cast<size_t>(b) * K * T : nullptr;
-  if (nbest) {
-    // padding of every row past its transcript
-    for (int r = 0; r < K; ++r) {
-      const int n = static_cast<int>(s_row[r]);
-      for (int tt = n + tid; tt < T; tt += kThreads) nbt[static_cast<size_t>(r) * T + tt] = -1;
-    }
-  }
-
-  // ---- traceback through the back-pointers, staged in LDS tiles ----
-  // 1-best: lane 0 of wave 0 walks the best slot.  N-best: lane j of wave 0
-  // walks slots j + 64 h (every live slot) and writes the rows of their ranks.
-  // (the LM.Final term is finite, so some slot is live exactly when the best
-  // final score is finite)
-  if (have && L > 0) {
-    const int tile_frames = kBigWords / K;
-    bool walker[SPL];
-    int jb[SPL], cnext[SPL], pos[SPL];
-    int32_t* orow[SPL];
-#pragma unroll
-    for (int h = 0; h < SPL; ++h) {
-      const int js = j + 64 * h;
-      walker[h] = (wave == 0) && (nbest ? (js < K && sc[h] != kNegInf) : (h == 0 && lane == 0));
-      jb[h] = nbest ? js : best;
-      cnext[h] = -1;
-      orow[h] = nullptr;
-      pos[h] = 0;
-      if (walker[h]) {
-        orow[h] = nbest ? nbt + static_cast<size_t>(s_row[KMX + js]) * T : ot;
-        pos[h] = nbest ? len[h] : nout;
-      }
-    }
-    for (int hi = L; hi > 0;) {
-      const int lo = hi > tile_frames ? hi - tile_frames : 0;
-      __syncthreads();
-      const int n = (hi - lo) * K;
-      const int32_t* src = bpb + static_cast<size_t>(lo) * K;
-      for (int q = tid; q < n; q += kThreads) s_big[q] = static_cast<uint32_t>(src[q]);
-      __syncthreads();
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        if (walker[h]) {
-          for (int tt = hi - 1; tt >= lo; --tt) {
-            const uint32_t e = s_big[(tt - lo) * K + jb[h]];
-            const int cl = static_cast<int>(e & 0xFFFFu);
-            const int par = static_cast<int>(e >> 16);
-            if (tt < L - 1 && cnext[h] != V && cnext[h] != cl) {
-              if (pos[h] > 0) {
-                --pos[h];
-                if (orow[h]) orow[h][pos[h]] = cnext[h];
-              }
-            }
-            cnext[h] = cl;
-            jb[h] = par;
-          }
-        }
-      }
-      hi = lo;
-    }
-    bool bad = false;
-#pragma unroll
-    for (int h = 0; h < SPL; ++h) {
-      if (walker[h]) {
-        if (cnext[h] != V && cnext[h] >= 0 && pos[h] > 0) {
-          --pos[h];
-          if (orow[h]) orow[h][pos[h]] = cnext[h];
-        }
-        bad = bad || pos[h] != 0;
-      }
-    }
-    if (wave == 0 && __ballot(bad) != 0ull) status |= 2u;
-  }
-  }
   if (tid == 0) {
     p.status[b] = status;
     if (b == 0) write_ws_header(p.ws_header, p.B);
   }
 }
 
-template <int LPT, int NLEV, int SPL, bool SKIP, bool REP, bool TREE>
-hipError_t launch_tree(const KernelParams& p, hipStream_t s) {
+template <int LPT, int NLEV, bool SKIP, bool REP>
+hipError_t launch_skip(const KernelParams& p, hipStream_t s) {
   dim3 grid(p.B), block(kThreads);
-  constexpr bool kCacheable = SPL == 1 && !SKIP && LPT >= 2 && NLEV > 0;
+  constexpr bool kCacheable = !SKIP && LPT >= 2 && NLEV > 0;
   if constexpr (REP) {
     // the repeat-scoring variant reads uncached rows; with neither an LM nor
     // boosting it has nothing to repeat (the caller takes the default kernel)
     if (p.bt_nodes != nullptr) {
-      hipLaunchKernelGGL((decode_kernel<LPT, NLEV, true, SPL, SKIP, false, true, TREE>), grid, block, 0, s, p);
+      hipLaunchKernelGGL((decode_kernel<LPT, NLEV, true, SKIP, false, true>), grid, block, 0, s, p);
     } else {
       if constexpr (NLEV < 0) return hipErrorInvalidValue;
-      else hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SPL, SKIP, false, true, TREE>), grid, block, 0, s, p);
+      else hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SKIP, false, true>), grid, block, 0, s, p);
     }
   } else if (p.bt_nodes != nullptr) {
-    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, true, SPL, SKIP, false, false, TREE>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, true, SKIP, false, false>), grid, block, 0, s, p);
   } else if (kCacheable && p.lm_states_below_2p23 && !(p.flags & kFlagNoRowCache)) {
-    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SPL, SKIP, kCacheable, false, TREE>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SKIP, kCacheable, false>), grid, block, 0, s, p);
   } else {
-    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SPL, SKIP, false, false, TREE>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SKIP, false, false>), grid, block, 0, s, p);
   }
   return hipGetLastError();
 }
 
-template <int LPT, int NLEV, int SPL, bool SKIP, bool REP>
-hipError_t launch_skip(const KernelParams& p, hipStream_t s) {
-  // the merge-tree rank for beams of 33..64 over several chunks
-  if constexpr (SPL == 1 && SKIP) {
-    if (p.K > 32) return launch_tree<LPT, NLEV, SPL, SKIP, REP, true>(p, s);
-  }
-  return launch_tree<LPT, NLEV, SPL, SKIP, REP, false>(p, s);
-}
-
-template <int LPT, int NLEV, int SPL, bool REP>
+template <int LPT, int NLEV, bool REP>
 hipError_t launch_nlev(const KernelParams& p, hipStream_t s) {
-  // beams of more than one chunk (16 / LPT rows) skip ranks
-  if constexpr (SPL > 1) {
-    return launch_skip<LPT, NLEV, SPL, true, REP>(p, s);
-  } else {
-    if (p.K > 16 / LPT) return launch_skip<LPT, NLEV, SPL, true, REP>(p, s);
-    return launch_skip<LPT, NLEV, SPL, false, REP>(p, s);
+  // beams of more than one chunk (16 / LPT rows) skip ranks; only the widest
+  // vocabularies, with an LM, take such beams here
+  if constexpr (LPT == 8 && NLEV >= 0) {
+    if (p.K > 16 / LPT) return launch_skip<LPT, NLEV, true, REP>(p, s);
   }
+  if (p.K > 16 / LPT) return hipErrorInvalidValue;
+  return launch_skip<LPT, NLEV, false, REP>(p, s);
 }
 
-template <int LPT, int SPL, bool REP>
-hipError_t launch_spl(const KernelParams& p, hipStream_t s) {
-  if (p.lm_states == nullptr && p.lm_arcs == nullptr) return launch_nlev<LPT, -1, SPL, REP>(p, s);
-  switch (p.lm_nlev) {
-    case 0: return launch_nlev<LPT, 0, SPL, REP>(p, s);
-    case 1: return launch_nlev<LPT, 1, SPL, REP>(p, s);
-    case 2: return launch_nlev<LPT, 2, SPL, REP>(p, s);
-    case 3: return launch_nlev<LPT, 3, SPL, REP>(p, s);
-    case 4: return launch_nlev<LPT, 4, SPL, REP>(p, s);
-    case 5: return launch_nlev<LPT, 5, SPL, REP>(p, s);
-    case 6: return launch_nlev<LPT, 6, SPL, REP>(p, s);
-    case 7: return launch_nlev<LPT, 7, SPL, REP>(p, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-// beams above 64 take two slots per lane (vocabularies of at most 1024
-// tokens; the host rejects the rest)
 template <int LPT, bool REP>
 hipError_t launch_lpt_impl(const KernelParams& p, hipStream_t s) {
-  if constexpr (LPT <= 2) {
-    if (p.K > 64) return launch_spl<LPT, 2, REP>(p, s);
-  } else {
-    if (p.K > 64) return hipErrorInvalidValue;
+  if (p.lm_states == nullptr && p.lm_arcs == nullptr) return launch_nlev<LPT, -1, REP>(p, s);
+  switch (p.lm_nlev) {
+    case 0: return launch_nlev<LPT, 0, REP>(p, s);
+    case 1: return launch_nlev<LPT, 1, REP>(p, s);
+    case 2: return launch_nlev<LPT, 2, REP>(p, s);
+    case 3: return launch_nlev<LPT, 3, REP>(p, s);
+    case 4: return launch_nlev<LPT, 4, REP>(p, s);
+    case 5: return launch_nlev<LPT, 5, REP>(p, s);
+    case 6: return launch_nlev<LPT, 6, REP>(p, s);
+    case 7: return launch_nlev<LPT, 7, REP>(p, s);
+    default: return hipErrorInvalidValue;
   }
-  return launch_spl<LPT, 1, REP>(p, s);
 }
 
 }  // namespace detail

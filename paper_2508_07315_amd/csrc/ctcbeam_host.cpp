@@ -47,6 +47,8 @@ using ctcbeam::LmLevel;
 struct ctcbeam_lm {
   int order = 0, V = 0, nlev = 0;
   int64_t n_states = 0, n_arcs = 0;
+  float absmax = 0.0f;           // bound of |ln P| of a finite query
+  float high = 0.0f;             // upper bound of a query
   std::vector<LmLevel> states;  // [n_states * nlev]
   std::vector<LmArc> arcs;
   std::vector<float> unigram;   // [V+1]
@@ -392,6 +394,20 @@ int build_lm_tables(int order, int V, const int64_t* counts, const int32_t* cons
   lm->nlev = nlev;
   lm->n_states = n_states;
   lm->n_arcs = n_arcs;
+  // bounds of a query: an entry plus a backoff weight of every level
+  float pmax = 0.0f, bmax = 0.0f, phigh = -std::numeric_limits<float>::infinity(), bhigh = 0.0f;
+  for (int m = 1; m <= order; ++m) {
+    for (const float v : ord[m].lnp) {
+      if (std::isfinite(v)) pmax = std::max(pmax, std::fabs(v));
+      phigh = std::max(phigh, v);
+    }
+    for (const float v : ord[m].lnbo) {
+      if (std::isfinite(v)) bmax = std::max(bmax, std::fabs(v));
+      bhigh = std::max(bhigh, v);
+    }
+  }
+  lm->absmax = pmax + static_cast<float>(nlev) * bmax;
+  lm->high = phigh + static_cast<float>(nlev) * bhigh;
   return 0;
 }
 
@@ -867,6 +883,8 @@ int decode_impl(const float* logprobs, const int32_t* lengths, int B, int T, int
     p.lm_nlev = lm->nlev;
     p.lm_states_below_2p23 = lm->n_states <= (int64_t(1) << 23) ? 1 : 0;
     p.lm_n_states = lm->n_states;
+    p.lm_absmax = lm->absmax;
+    p.lm_max = lm->high;
     p.lm_bos_state = static_cast<uint32_t>(V);
   }
   if (boost) {

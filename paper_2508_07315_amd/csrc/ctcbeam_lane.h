@@ -77,6 +77,11 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_movf(float v, float old) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
+// value of the lane D below within each 16-lane row; all ones from outside it
+template <int D>
+__device__ __forceinline__ uint32_t dpp_shr_ones(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(-1, static_cast<int>(v), 0x110 + D, 0xF, 0xF, false));
+}
 constexpr int kDppQuadXor1 = 0xB1;  // quad_perm [1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;  // quad_perm [2,3,0,1]
 constexpr int kDppRowShl4 = 0x104;
@@ -221,6 +226,54 @@ __device__ __forceinline__ uint32_t row_ge_count(float v) {
 template <int N>
 __device__ __forceinline__ float wave_sort_desc(float v, int lane) {
   return bitonic_levels<N, 2>(v, lane);
+}
+
+// ---- fp32 log-sum-exp of the log-sum-exp recombination variant ----
+// Every step is one IEEE fp32 operation in a fixed order (no contraction), so
+// the result is reproducible bit for bit.  exp(d), -80 <= d <= 0: Cody-Waite
+// reduction d = k ln2 + r with k = rint(d / ln2) and ln2 split into a 9-bit
+// head (k * head is exact) and a tail, the degree-7 Taylor polynomial of e^r
+// by Horner, times 2^k built from its exponent bits.
+__device__ __forceinline__ float exp32_nonpos(float d) {
+  const float k = __builtin_rintf(d * 1.44269504f);
+  const float r = (d - k * 0.693359375f) - k * -2.12194440e-4f;
+  float q = 1.0f / 5040.0f;
+  q = q * r + 1.0f / 720.0f;
+  q = q * r + 1.0f / 120.0f;
+  q = q * r + 1.0f / 24.0f;
+  q = q * r + 1.0f / 6.0f;
+  q = q * r + 0.5f;
+  q = q * r + 1.0f;
+  q = q * r + 1.0f;
+  return q * __uint_as_float(static_cast<uint32_t>(static_cast<int>(k) + 127) << 23);
+}
+// log(1 + e), 2^-24 <= e <= 1: 2 atanh(s) with s = e / (2 + e) <= 1/3, the odd
+// series to s^17 by Horner in s^2.
+__device__ __forceinline__ float log1p32_unit(float e) {
+  const float s = e / (2.0f + e);
+  const float z = s * s;
+  float q = 1.0f / 17.0f;
+  q = q * z + 1.0f / 15.0f;
+  q = q * z + 1.0f / 13.0f;
+  q = q * z + 1.0f / 11.0f;
+  q = q * z + 1.0f / 9.0f;
+  q = q * z + 1.0f / 7.0f;
+  q = q * z + 1.0f / 5.0f;
+  q = q * z + 1.0f / 3.0f;
+  q = q * z + 1.0f;
+  const float t = s * q;
+  return t + t;
+}
+// log(exp(a) + exp(b))
+__device__ __forceinline__ float lse32(float a, float b) {
+  const float hi = (a < b) ? b : a;
+  const float lo = (a < b) ? a : b;
+  if (lo == kNegInf) return hi;
+  const float d = lo - hi;
+  if (d < -80.0f) return hi;
+  const float e = exp32_nonpos(d);
+  const float l = (e < 5.9604645e-8f) ? e : log1p32_unit(e);
+  return hi + l;
 }
 
 }  // namespace detail

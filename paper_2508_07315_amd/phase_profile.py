@@ -9,11 +9,13 @@ counters at every phase boundary), then on a GPU:
 
 Prints, per phase of the frame step (beam search: fill, barrier A,
 candidates, barrier B, bound, filter, barrier C, rank, barrier D, and the update
-as prune + recombination, new state, chunk plan and the rest; greedy:
+as prune + recombination, new state, chunk plan and the rest; the class
+decoder, which serves beams over one chunk: plan, fill, barrier A, scoring,
+barrier B, bound, expansion, barrier C, rank, barrier D, update; greedy:
 scoring, the wave's best, the exchange barrier, the decision, chain headers +
 fold, continuations, log-prob row loads), the mean cycles per frame of each
 wave, averaged over the utterances (weighted by their frames), and the mean
-chunks (refills) per frame.  Inputs are the seeded workloads of ``workloads``.
+chunks (passes, refills) per frame.  Inputs are the seeded workloads of ``workloads``.
 """
 from __future__ import annotations
 
@@ -23,11 +25,14 @@ import os
 import sys
 
 # (counter word, name); the beam update is split into prune + recombination,
-# new state, chunk plan and the rest (one slot per lane; two slots per lane
-# count the whole update under "upd rest")
+# new state, chunk plan and the rest.  The class decoder counts its classes in
+# word 12, which the general decoder uses as a clock: it is told apart by word
+# 19 (pairs expanded), which only it counts.
 PHASES = {"beam": [(0, "fill"), (1, "bar A"), (2, "cand"), (3, "bar B"), (14, "bound"), (4, "filter"), (5, "bar C"),
                    (6, "rank"), (7, "bar D"), (11, "upd merge"), (12, "upd state"), (13, "upd plan"),
                    (8, "upd rest")],
+          "class": [(13, "plan"), (0, "fill"), (1, "bar A"), (2, "cand"), (3, "bar B"), (14, "bound"),
+                    (4, "expand"), (5, "bar C"), (6, "rank"), (7, "bar D"), (8, "update")],
           "greedy": list(enumerate(["score", "best", "barrier", "decide", "hdr+fold", "arcs", "rows"]))}
 WAVES = 8
 WORDS = 20
@@ -82,20 +87,25 @@ def main(argv=None):
     frames = ph[:, 0, 9]
     chunks = ph[:, 0, 10]
     nf = frames.sum()
-    what = "refills" if args.mode == "greedy" else "chunks"
+    kind = "class" if args.mode == "beam" and ph[:, :, 19].sum() > 0 else args.mode
+    what = {"greedy": "refills", "class": "passes", "beam": "chunks"}[kind]
     print(f"{w.name} {args.mode} K={1 if args.mode == 'greedy' else w.K} theta={theta}: {int(nf)} frames, "
           f"{chunks.sum() / max(nf, 1):.2f} {what}/frame")
     print("cycles per frame by wave (mean over utterances, weighted by frames)")
     print("phase     " + " ".join(f"{'w%d' % q:>7s}" for q in range(WAVES)) + "     mean")
     tot = np.zeros(WAVES)
-    for k, name in PHASES[args.mode]:
+    for k, name in PHASES[kind]:
         per = ph[:, :, k].sum(axis=0) / max(nf, 1)
         tot += per
         print(f"{name:9s} " + " ".join(f"{v:7.0f}" for v in per) + f"  {per.mean():7.0f}")
     print(f"{'total':9s} " + " ".join(f"{v:7.0f}" for v in tot) + f"  {tot.mean():7.0f}")
-    if args.mode == "beam":
+    if kind == "class":
         per = lambda k: ph[:, 0, k].sum() / max(nf, 1)
-        print(f"ranks per frame {per(15):.2f} (block or merge-tree ranks of more than 64 entries "
+        print(f"classes per frame {per(12):.1f}, rows filled (LM {per(16):.2f}, boosting {per(18):.2f}), "
+              f"pairs expanded by wave 0 {per(19):.1f}, pool entries {per(15):.0f}, overflows {per(17):.3f}")
+    elif kind == "beam":
+        per = lambda k: ph[:, 0, k].sum() / max(nf, 1)
+        print(f"ranks per frame {per(15):.2f} (block ranks of more than 64 entries "
               f"{per(16):.2f}), pool overflows per frame {per(17):.3f}")
 
 

@@ -1,0 +1,87 @@
+"""GPU parity of the class decoder (beams over one chunk of the general
+decoder) at the sizes where its split changes: labels at the edges of the lane
+sets that share the classes (64, 128, 256 and 512 tokens) and of the labels per
+lane (1024, 2048), beam sizes at the edges of a register set (64), of the
+duplicate search (16) and of the pool, and row shortage (vocabularies whose
+rows hold few states, so that a frame takes several passes).  Against the CPU
+oracle, N-best: tokens and lengths equal, scores within 1e-4."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_2508_07315_amd as P
+import workloads as W
+from gpu_helpers import device, gpu_boost, gpu_lm, log, oracle_bt, oracle_lm, oracle_threads
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # V, K, order, phrases, theta, flags
+    (2, 128, 0, 0, math.inf, {}),
+    (64, 9, 3, 20, math.inf, {}),
+    (65, 17, 3, 20, 12.0, {}),
+    (128, 64, 2, 0, math.inf, {"logsumexp": True}),
+    (129, 65, 0, 40, math.inf, {}),
+    (256, 33, 3, 0, 12.0, {"repeat_score": True}),
+    (257, 128, 3, 60, 12.0, {"logsumexp": True, "boost_rollback": True}),
+    (512, 17, 2, 60, math.inf, {"repeat_score": True}),
+    (513, 128, 4, 60, 12.0, {}),
+    (1023, 16, 3, 200, math.inf, {}),
+    (1024, 64, 3, 200, math.inf, {"row_cache": False}),
+    (1025, 12, 3, 200, math.inf, {}),
+    (2047, 5, 0, 100, math.inf, {}),
+    (2049, 3, 2, 100, 12.0, {}),
+    (2560, 16, 3, 2000, math.inf, {}),
+    (3072, 9, 3, 0, math.inf, {"repeat_score": True}),
+    (4096, 40, 3, 3000, 12.0, {}),
+    (4095, 64, 0, 0, math.inf, {"logsumexp": True}),
+]
+
+
+@pytest.mark.parametrize("V,K,order,phrases,theta,kw", CASES)
+def test_class_decoder(V, K, order, phrases, theta, kw):
+    import torch
+    B, T = 3, 36
+    rng = np.random.default_rng([V, K])
+    lp = W.random_logprobs(rng, B, T, V)
+    lens = np.array([T, 19, 1], dtype=np.int32)
+    counts = (min(6 * V, V * V), 4 * V, 2 * V)[: order - 1] if order else ()
+    spec = W.LMSpec(order=order, counts=counts, seed=V + K) if order else None
+    bspec = W.BoostSpec(phrases, 2, 4, "zipf", V) if phrases else None
+    log("class decoder", V, K, order, phrases, theta, kw)
+    dev = device()
+    alpha, w = (0.5 if order else 0.0), (1.25 if phrases else 0.0)
+    tok, ln, sc, ws = P.ctcbeam_decode_nbest(
+        torch.from_numpy(lp).to(dev), torch.from_numpy(lens).to(dev), K, alpha, 1.0, w,
+        gpu_lm(spec, V) if spec else None, gpu_boost(bspec, V) if bspec else None, theta=theta, **kw)
+    torch.cuda.synchronize()
+    assert P.ctcbeam_query_status(ws) == 0
+    okw = {k: v for k, v in kw.items() if k != "row_cache"}
+    r = oracle.decode(lp, lens, K, alpha, 1.0, w, theta=theta, lm=oracle_lm(spec, V) if spec else None,
+                      bt=oracle_bt(bspec, V) if bspec else None, n_threads=oracle_threads(), want_nbest=True, **okw)
+    np.testing.assert_array_equal(ln.cpu().numpy(), r["nbest_lengths"])
+    np.testing.assert_array_equal(tok.cpu().numpy(), r["nbest_tokens"])
+    np.testing.assert_allclose(sc.cpu().numpy(), r["nbest_scores"], rtol=0, atol=1e-4)
+
+
+@pytest.mark.parametrize("V,K", [(40, 12), (700, 40), (1024, 128), (3000, 64)])
+def test_ties_overflow_the_pool(V, K):
+    """Rows of equal values: every label ties, so the candidates at the bound
+    exceed the pool and the index order decides."""
+    import torch
+    B, T = 2, 7
+    lp = np.full((B, T, V + 1), -math.log(V + 1), dtype=np.float32)
+    lp[1, 2:, V] = -0.5
+    lp[1, 4] = -np.inf
+    lp[1, 4, : V // 2] = -2.0
+    lens = np.array([T, T], dtype=np.int32)
+    log("ties", V, K)
+    dev = device()
+    tok, ln, sc, ws = P.ctcbeam_decode_nbest(torch.from_numpy(lp).to(dev), torch.from_numpy(lens).to(dev), K, 0.0, 0.25)
+    torch.cuda.synchronize()
+    assert P.ctcbeam_query_status(ws) == 0
+    r = oracle.decode(lp, lens, K, 0.0, 0.25, want_nbest=True)
+    np.testing.assert_array_equal(tok.cpu().numpy(), r["nbest_tokens"])
+    np.testing.assert_allclose(sc.cpu().numpy(), r["nbest_scores"], rtol=0, atol=1e-4)
