@@ -5,23 +5,41 @@
 // fold x = s_k + D[c], x += beta for emitting labels; TopK by (score desc,
 // flat index asc); pruning; recombination; read-out of the hypothesis trie,
 // Sec. III-A), laid out for the beam sizes of the paper's main tables
-// (K = 4..8) without a language model:
+// (K = 4..8) without a language model.
 //
-// * one workgroup of 4 wave64 per utterance, one wave per SIMD; lane l of
-//   wave w scores labels c = 64w + l + 256j, j < 4, for every live beam;
-// * the beam itself (scores, last labels, transcript hashes and lengths)
-//   lives in registers of wave 0 only (slot k in lane k): the selection and
-//   the update run once, in that wave, instead of in every wave.
+// What bounds it is the serial chain of the frames: the beam of frame t is
+// known only when frame t - 1 is done.  The work that does not depend on the
+// beam is therefore taken out of that chain.  Without models a label's score
+// depends on the beam only through s_k, and fp32 addition is monotone, so the
+// candidates of every beam are ordered as D is, and the K best of a frame lie
+// among few (beam, label rank) positions: with the live beams in descending
+// order of score, a candidate of beam i with the label of rank r (rank by D
+// descending, label ascending) has at least (i + 1) r - 1 emitting candidates
+// of no lower score before it (each beam's repeat label, which emits nothing,
+// is taken off), so those with (i + 1) r > K are not needed.  That leaves
+// sum_i (K / (i + 1) + 1) = 28 candidates at K = 8; with 8 blanks and 8
+// repeats a frame's selection is 44 entries: one per lane of one wave.
 //
-// Per frame: S (all waves) score every candidate in registers and publish
-// the maxima of (beam, wave) groups; barrier; F (all waves) take the K-th
-// largest group maximum (and, with K live beams, the smallest blank score) as
-// a lower bound of the K-th best candidate and write the candidates at or
-// above it to per-wave survivor segments; barrier; R (wave 0) ranks the blank
-// candidates and the survivors exactly, builds the successors, prunes,
-// recombines and writes the back-pointers; barrier.  More than 64 ranked
-// entries (mass ties) fall back to an exact K-step extraction over all
-// candidates.
+// One workgroup of 4 wave64 per utterance, one wave per SIMD:
+// * waves 1..3 make, a batch of frames ahead, each frame's list of its K + 2
+//   best labels (a bound from the lane maxima, the values that reach it
+//   gathered, ranked by counting) and leave the row in LDS for the repeats;
+// * wave 0 runs the chain alone, without a barrier inside a batch: read the
+//   beam, one candidate per lane, rank by counting, successors, prune,
+//   recombine.
+//
+// A candidate left out ties the K-th best at most.  K further lanes carry the
+// best score left out of each beam; when one of them reaches the K-th best, or
+// two entries have equal scores, the frame is settled by the exact keys
+// (score, flat index), and the places at the K-th best score go to the lowest
+// flat indices of all candidates with that score.
+//
+// Measured against the form it replaces (every wave scored its labels for
+// every beam and published maxima; three barriers a frame): 32 utterances of
+// 400 frames, V = 1024, K = 8: 1.48 -> 0.68 ms; one utterance of 50 frames,
+// V = 32, K = 4: 0.109 -> 0.044 ms.  The chain of wave 0 bounds it (about 1.7
+// us a frame at K = 8): the lists cost nothing that shows, in a form with two
+// frames side by side or one after the other.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -39,57 +57,138 @@ using detail::rdlane;
 
 constexpr int kST = 256;             // threads: 4 wave64
 constexpr int kSW = kST / 64;        // waves
-constexpr int kLPL = 4;              // labels per lane
-constexpr int kVmax = kST * kLPL;    // 1024 labels (blank handled apart)
+constexpr int kVmax = 1024;          // labels (blank handled apart)
 constexpr int kKmax = 8;             // beam slots
-constexpr int kSeg = 64;             // survivor entries per wave
-constexpr int kStage = 2048;         // 64-bit words of the traceback tiles
+constexpr int kFP = 2;               // frames a list wave makes per batch
+constexpr int kF = kFP * (kSW - 1);  // frames of a batch
+constexpr int kList = kKmax + 2;     // list entries of a frame
+constexpr int kGather = 64;          // values gathered for a list
 
-// value of lane (lane ^ j) for compile-time j, with the lane masks
-// materialised where they are used (a frame loop would otherwise keep every
-// 64-bit mask live in scalar registers)
-template <int J>
-__device__ __forceinline__ uint32_t xlane(uint32_t v) {
-  if constexpr (J == 1) return detail::dpp_full<detail::kDppQuadXor1>(v);
-  else if constexpr (J == 2) return detail::dpp_full<detail::kDppQuadXor2>(v);
-  else if constexpr (J == 4) {
-    const uint32_t up = detail::dpp_mov<detail::kDppRowShl4>(v);
-    const uint32_t dn = detail::dpp_mov<detail::kDppRowShr4>(v);
-    return detail::lane_in_here<detail::kLanesBit2>() ? dn : up;
-  } else if constexpr (J == 8) return detail::dpp_full<detail::kDppRowRor8>(v);
-  else if constexpr (J == 16) {
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    return detail::lane_in_here<detail::kLanesBit4>() ? static_cast<uint32_t>(r[0]) : static_cast<uint32_t>(r[1]);
-  } else {
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return detail::lane_in_here<detail::kLanesBit5>() ? static_cast<uint32_t>(r[0]) : static_cast<uint32_t>(r[1]);
+// order of LDS accesses between lanes of one wave (LDS operations of a wave
+// complete in issue order, so the compiler has to keep it)
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+// barrier for LDS data: global loads of the next batch stay in flight over it
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// One frame's M best labels by value descending and label ascending, where the
+// gather does not hold all values that reach the bound tau (ties, or many
+// labels of few lanes): M rounds of "best key below the previous one".
+template <int NJ>
+__device__ __forceinline__ void extract_list(const float (&v)[NJ], int M, int lane, uint2* list) {
+  uint64_t prev = ~0ull;
+#pragma unroll 1
+  for (int r = 0; r < M; ++r) {
+    uint64_t best = 0ull;
+    float bv = kNegInf;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const uint64_t key = v[j] != kNegInf ? order_key(v[j], static_cast<uint32_t>(lane + 64 * j)) : 0ull;
+      if (key < prev && key > best) {
+        best = key;
+        bv = v[j];
+      }
+    }
+    uint64_t wb = best;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint64_t o = __shfl_xor(wb, off);
+      wb = o > wb ? o : wb;
+    }
+    if (wb == 0ull) break;  // uniform: nothing finite left
+    if (best == wb) list[r] = make_uint2(__float_as_uint(bv), 0xFFFFFFFFu - static_cast<uint32_t>(wb));
+    prev = wb;
   }
 }
-template <int J>
-__device__ __forceinline__ float xlanef(float v) { return __uint_as_float(xlane<J>(__float_as_uint(v))); }
 
+// The M best labels of each of NQ frames, by value descending and label
+// ascending; lane l holds labels l + 64 j (-inf past V and for NaN) and the
+// frames' rows are in LDS.  list[q] gets (value, label) pairs, entries past the
+// finite values (-inf, V).  The frames go through each step together: a step
+// is a chain of dependent instructions.
+template <int NJ, int NQ, int GS, int LS, int RS>
+__device__ __forceinline__ void make_lists(const float (&v)[NQ][NJ], int M, int V, int lane, const float* row,
+                                           uint64_t* gather, uint2* list) {
+  float tau[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    float top = v[q][0];
+#pragma unroll
+    for (int j = 1; j < NJ; ++j) top = fmaxf(top, v[q][j]);
+    tau[q] = detail::wave_sort_desc<64>(top, lane);
+  }
+  uint32_t bits[NQ];
+  int n[NQ], at[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    // M lanes reach the M-th largest lane maximum, so the M best values do
+    const float t = rdlane(tau[q], M - 1);
+    bits[q] = 0u;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) bits[q] |= (v[q][j] >= t && v[q][j] != kNegInf) ? (1u << j) : 0u;
+    const int cnt = __popc(bits[q]);
+    const int incl = detail::wave_incl_scan(cnt, lane);
+    n[q] = rdlane(incl, 63);
+    at[q] = incl - cnt;
+    if (lane < M) list[q * LS + lane] = make_uint2(__float_as_uint(kNegInf), static_cast<uint32_t>(V));
+    gather[q * GS + lane] = 0ull;
+  }
+  wave_lds_fence();
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    if (n[q] <= kGather) {  // uniform
+      for (uint32_t m = bits[q]; m != 0u; m &= m - 1u) {  // usually none or one
+        const uint32_t c = static_cast<uint32_t>(lane + 64 * __builtin_ctz(m));
+        gather[q * GS + at[q]++] = order_key(row[q * RS + c], c);
+      }
+    }
+  }
+  wave_lds_fence();
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    if (n[q] <= kGather) {  // uniform
+      const uint64_t key = gather[q * GS + lane];  // 0: none
+      int rank = 0;
+#pragma unroll
+      for (int i = 0; i < 10; ++i) {
+        const ulonglong2 o = reinterpret_cast<const ulonglong2*>(gather + q * GS)[i];
+        rank += (o.x > key ? 1 : 0) + (o.y > key ? 1 : 0);
+      }
+      for (int i = 10; 2 * i < n[q]; ++i) {  // uniform trip count
+        const ulonglong2 o = reinterpret_cast<const ulonglong2*>(gather + q * GS)[i];
+        rank += (o.x > key ? 1 : 0) + (o.y > key ? 1 : 0);
+      }
+      if (key != 0ull && rank < M) {
+        const uint32_t c = 0xFFFFFFFFu - static_cast<uint32_t>(key);
+        list[q * LS + rank] = make_uint2(__float_as_uint(row[q * RS + c]), c);
+      }
+    } else {
+      extract_list<NJ>(v[q], M, lane, list + q * LS);
+    }
+  }
+}
+
+// NJ = labels per lane of a list wave (V <= 64 NJ)
+template <int NJ>
 __global__ void __launch_bounds__(kST) small_kernel(KernelParams p) {
-  // back-pointer tiles of the traceback
-  __shared__ __align__(16) uint64_t s_big[kStage];
-
-  // this frame's candidates: [live position][thread] -> labels tid + 256 j
-  __shared__ __align__(16) float4 s_cand[kKmax * kST];
-  __shared__ uint4 s_seg[kSW][kSeg];     // survivors: score bits, flat index, 0, emits
-  __shared__ int s_nseg[kSW];
-  __shared__ int s_ovf;
-  __shared__ float s_gmax[kSW * kKmax];  // (beam, wave) maxima
+  constexpr int kRow = NJ * 64 + 4;  // labels and the blank of a frame
+  constexpr int kRowWords = 2 * kF * kRow;
+  constexpr int kStageWords = kRowWords > 4096 ? kRowWords : 4096;
+  // rows of two batches of frames; the traceback's tiles after the last frame
+  __shared__ __align__(16) uint32_t s_big[kStageWords];
+  __shared__ uint2 s_list[2][kF][kList];  // (value, label)
+  __shared__ __align__(16) uint64_t s_gather[kSW - 1][kFP][kGather];
+  __shared__ int s_bp[2][kF * kKmax];     // back-pointers of a batch
   // the beam as the scoring sees it, by live position (slot order; dead
-  // positions score -inf): score bits, last label, 0, slot * W
-  __shared__ uint4 s_beam[2][kKmax];  // [frame & 1] read by frame t
-  __shared__ int s_nlive;
-  // exact extraction (fallback): winners in rank order; wave maxima
-  __shared__ uint4 s_win[kKmax];
-  __shared__ __align__(16) uint64_t s_key[64];  // ranked keys (wave 0)
-  // the beam's slot records (wave 0 writes them after each update): hash lo,
-  // hi, length
-  constexpr int kSlotWords = 4;
-  __shared__ __align__(16) uint32_t s_slot[kKmax][kSlotWords];
-  __shared__ uint64_t s_red[2][kSW];
+  // positions score -inf): score bits, last label, slot, the last label's
+  // value in the frame
+  __shared__ uint4 s_beam[kKmax];
+  __shared__ __align__(16) float s_x[64];       // scores ranked
+  __shared__ __align__(16) uint64_t s_key[64];  // keys ranked (equal scores)
+  __shared__ uint32_t s_tie[kKmax];             // winners at the K-th best score
   __shared__ int s_best, s_bestlen;
   __shared__ float s_bestscore;
   __shared__ int s_nblen[kKmax], s_nbrank[kKmax];
@@ -108,319 +207,260 @@ __global__ void __launch_bounds__(kST) small_kernel(KernelParams p) {
   if (L > T) { L = T; status |= 1u; }
   const float* Db = p.logprobs + static_cast<size_t>(b) * T * W;
   int32_t* bpb = p.bp + static_cast<size_t>(b) * T * K;
-
-  float rD[kLPL], rDn[kLPL];
-#pragma unroll
-  for (int j = 0; j < kLPL; ++j) {
-    const int c = tid + j * kST;
-    rDn[j] = (c < V && L > 0) ? Db[c] : kNegInf;
-    rD[j] = kNegInf;
-  }
+  float* const s_row = reinterpret_cast<float*>(s_big);
+  const int nbatch = (L + kF - 1) / kF;
 
   // ---- the beam (wave 0, slot k in lane k) ----
   float sc = (lane == 0) ? 0.0f : kNegInf;
   int last = V, len = 0;
   uint32_t hlo = 0u, hhi = 0u;
-
   // counters (wave 0 lanes, summed at the end)
   uint32_t st_alive = 0u, st_emit = 0u;
 
-  if (tid < kKmax) {
-    // slot records: slot 0 is the initial (empty) beam, the others never parents
-#pragma unroll
-    for (int w = 0; w < kSlotWords; ++w) s_slot[tid][w] = 0u;
-    s_beam[0][tid] = make_uint4(__float_as_uint(tid == 0 ? 0.0f : kNegInf), static_cast<uint32_t>(V), 0u, 0u);
+  // ---- wave 0: the entry of this lane ----
+  // emitting candidates (position ei, label rank er), then the blanks, the
+  // repeats and the best candidates left out (er = K / (ei + 1) + 1)
+  int ei = 0, er = 0, nent = 0;
+  bool k_emit = false, k_blank = false, k_rep = false, k_out = false;
+  {
+    int at = 0;
+    for (int i = 0; i < K; ++i) {
+      const int n = K / (i + 1) + 1;
+      if (lane >= at && lane < at + n) {
+        k_emit = true;
+        ei = i;
+        er = lane - at;
+      }
+      at += n;
+    }
+    nent = at + 2 * K;
+    const int q = lane - at;
+    if (q >= 0 && q < 3 * K) {
+      const int g = q / K;
+      ei = q - g * K;
+      k_blank = g == 0;
+      k_rep = g == 1;
+      k_out = g == 2;
+      if (k_out) er = K / (ei + 1) + 1;
+    }
   }
-  if (tid == 0) {
-    s_nlive = L > 0 ? 1 : 0;
-    s_ovf = 0;
+  const bool k_label = k_emit || k_out;  // lanes that read the list
+
+  // ---- waves 1..3: frames ahead ----
+  // (frames past the end repeat the last one; nothing reads them)
+  float rn[kFP][NJ], rb[kFP];
+  const auto load_rows = [&](int n) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < kFP; ++q) {
+      const int t = min(n * kF + (wave - 1) * kFP + q, L - 1);
+      const float* rowp = Db + static_cast<size_t>(t) * W;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) rn[q][j] = __builtin_nontemporal_load(rowp + min(lane + 64 * j, V));
+      rb[q] = rowp[V];
+    }
+  };
+  const auto make_frames = [&](int n) __attribute__((always_inline)) {
+    const int f0 = (n & 1) * kF + (wave - 1) * kFP;
+    float* row = s_row + f0 * kRow;
+    float v[kFP][NJ];
+#pragma unroll
+    for (int q = 0; q < kFP; ++q) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int c = lane + 64 * j;
+        const float d = rn[q][j];
+        v[q][j] = (c < V && d == d) ? d : kNegInf;
+        if (c < V) row[q * kRow + c] = v[q][j];
+      }
+      if (lane == 0) row[q * kRow + V] = rb[q];
+    }
+    make_lists<NJ, kFP, kGather, kList, kRow>(v, K + 2, V, lane, row, s_gather[wave - 1][0],
+                                              &s_list[0][0][0] + f0 * kList);
+  };
+  // back-pointers of batch n to global memory
+  const auto store_bp = [&](int n) __attribute__((always_inline)) {
+    const int cnt = min(kF, L - n * kF) * K;
+    if (wave == 1 && lane < cnt) bpb[static_cast<size_t>(n) * kF * K + lane] = s_bp[n & 1][lane];
+  };
+  static_assert(kF * kKmax <= 64, "a batch's back-pointers are stored by one wave");
+
+  if (wave == 0) {
+    if (lane < kKmax)
+      s_beam[lane] = make_uint4(__float_as_uint(lane == 0 ? 0.0f : kNegInf), static_cast<uint32_t>(V), 0u, 0u);
+  } else if (nbatch > 0) {
+    load_rows(0);
   }
-  __syncthreads();
 
-  for (int t = 0; t < L; ++t) {
-    const int cb = t & 1;  // double buffers read by this frame
-    // labels past V read the row's blank and score -inf (the prefetched
-    // values are used only here, a frame after their loads were issued)
-#pragma unroll
-    for (int j = 0; j < kLPL; ++j) rD[j] = (tid + j * kST < V) ? rDn[j] : kNegInf;
-    if (t + 1 < L) {
-      const float* rowp = Db + static_cast<size_t>(t + 1) * W;
-#pragma unroll
-      for (int j = 0; j < kLPL; ++j) rDn[j] = __builtin_nontemporal_load(rowp + min(tid + j * kST, V));
-    }
-    const float dblank = Db[static_cast<size_t>(t) * W + V];
-    const int nlive = __builtin_amdgcn_readfirstlane(s_nlive);
-
-    // ---- S. candidates of every beam position, straight-line ----
-    uint4 brec[kKmax];
-#pragma unroll
-    for (int i = 0; i < kKmax; ++i) brec[i] = s_beam[cb][i];  // broadcast reads
-    float cand[kKmax][kLPL];
-    float rmax[kKmax];
-#pragma unroll
-    for (int i = 0; i < kKmax; ++i) {
-      const float si = __uint_as_float(brec[i].x);
-      const int lasti = static_cast<int>(brec[i].y);
-#pragma unroll
-      for (int j = 0; j < kLPL; ++j) {
-        const int c = tid + j * kST;
-        const float x0 = si + rD[j];
-        const float x = x0 + beta;
-        // the repeat of the beam's last frame label emits nothing
-        cand[i][j] = (c == lasti) ? x0 : x;
+  // round n: wave 0 decodes batch n, waves 1..3 make batch n + 1
+  for (int n = -1; n < nbatch; ++n) {
+    if (wave != 0) {
+      if (n + 1 < nbatch) {
+        make_frames(n + 1);
+        if (n + 2 < nbatch) load_rows(n + 2);
       }
-      rmax[i] = fmaxf(fmaxf(cand[i][0], cand[i][1]), fmaxf(cand[i][2], cand[i][3]));
-      s_cand[i * kST + tid] = make_float4(cand[i][0], cand[i][1], cand[i][2], cand[i][3]);
-    }
-    {
-      // wave maxima of the 8 beam groups: a transposed reduction halves the
-      // groups a lane carries at lane-bit steps 1, 2, 4, then reduces over
-      // lane bits 3..5; lane l ends with group 4(l&1) + 2(l>>1&1) + (l>>2&1)
-      const bool b0 = detail::lane_in_here<0xAAAAAAAAAAAAAAAAull>();
-      float m4[4], m2[2];
+      if (n > 0) store_bp(n - 1);
+    } else if (n >= 0) {
+      const int nf = min(kF, L - n * kF);
+      for (int f = 0; f < nf; ++f) {
+        const float* row = s_row + ((n & 1) * kF + f) * kRow;
+        wave_lds_fence();
+        const uint4 br = s_beam[ei];
+        const uint2 le = s_list[n & 1][f][er];
+        const float dblank = row[V];
+        const float si = __uint_as_float(br.x);
+        const int li = static_cast<int>(br.y);
+        float drep = __uint_as_float(br.w);
+        if (f == 0) drep = row[li];  // the batch's first row was not there before
+        // the candidate of this lane
+        const int c = k_label ? static_cast<int>(le.y) : k_rep ? li : V;
+        const float d = k_label ? __uint_as_float(le.x) : k_rep ? drep : dblank;
+        float x = si + d;
+        const float xe = x + beta;
+        x = k_label ? xe : x;
+        // the repeat of the beam's last frame label emits nothing; no repeat
+        // after a blank; NaN candidates of labels are none
+        if (!k_blank && (k_rep ? li == V : (c == li && !k_out))) x = kNegInf;
+        if (!k_blank && !(x == x)) x = kNegInf;
+        if (!(k_emit || k_blank || k_rep || k_out)) x = kNegInf;
+        const float xo = k_out ? x : kNegInf;  // the best candidate left out of position ei
+        if (k_out) x = kNegInf;
+        const bool evalid = x != kNegInf;
+        s_x[lane] = x;
+        wave_lds_fence();
+        int r0 = 0, r1 = 0, r2 = 0, r3 = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        m4[q] = fmaxf(b0 ? rmax[q + 4] : rmax[q], xlanef<1>(b0 ? rmax[q] : rmax[q + 4]));
-      const bool b1 = detail::lane_in_here<0xCCCCCCCCCCCCCCCCull>();
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-        m2[q] = fmaxf(b1 ? m4[q + 2] : m4[q], xlanef<2>(b1 ? m4[q] : m4[q + 2]));
-      const bool b2 = detail::lane_in_here<detail::kLanesBit2>();
-      float m1 = fmaxf(b2 ? m2[1] : m2[0], xlanef<4>(b2 ? m2[0] : m2[1]));
-      m1 = fmaxf(m1, xlanef<8>(m1));
-      m1 = fmaxf(m1, xlanef<16>(m1));
-      m1 = fmaxf(m1, xlanef<32>(m1));
-      if (lane < kKmax) s_gmax[wave * kKmax + lane] = m1;
-    }
-    if (tid == 0) s_ovf = 0;
-    __syncthreads();  // B1: group maxima, candidates
-
-    // ---- F. bound and survivors ----
-    {
-      // K-th largest of the (beam, wave) maxima: maxima of disjoint groups
-      // are distinct candidates, so at least K candidates reach it
-      float g = lane < kSW * kKmax ? s_gmax[lane] : kNegInf;
-      g = detail::wave_sort_desc<32>(g, lane);
-      float tau = rdlane(g, K - 1);
-      if (nlive == K) {
-        // the K blank candidates: the K-th best is at least their minimum
-        float tb = __builtin_huge_valf();
-#pragma unroll
-        for (int i = 0; i < kKmax; ++i)
-          if (i < K) tb = detail::fmin_sel(tb, __uint_as_float(brec[i].x) + dblank);
-        tau = fmaxf(tau, tb);
-      }
-      // an infinite bound admits every finite candidate and no -inf one
-      tau = fmaxf(tau, -__FLT_MAX__);
-      uint32_t q = 0u;
-#pragma unroll
-      for (int i = 0; i < kKmax; ++i) {
-        if (__ballot(rmax[i] >= tau) != 0ull) {  // uniform
-#pragma unroll
-          for (int j = 0; j < kLPL; ++j) q |= (cand[i][j] >= tau) ? (1u << (i * kLPL + j)) : 0u;
+        for (int q = 0; q < 5; ++q) {
+          const float4 o = reinterpret_cast<const float4*>(s_x)[q];
+          r0 += o.x > x ? 1 : 0;
+          r1 += o.y > x ? 1 : 0;
+          r2 += o.z > x ? 1 : 0;
+          r3 += o.w > x ? 1 : 0;
         }
-      }
-      const int cnt = __popc(q);
-      const int incl = detail::wave_incl_scan(cnt, lane);
-      const int tot = rdlane(incl, 63);
-      if (tot > kSeg) {
-        if (lane == 0) s_ovf = 1;
-      } else {
-        int at = incl - cnt;
-        for (uint32_t qq = q; qq != 0u; qq &= qq - 1u) {  // a lane's survivors (usually none)
-          const int r = __builtin_ctz(qq);
-          const int i = r >> 2;
-          const uint32_t c = static_cast<uint32_t>(tid + (r & 3) * kST);
-          const float x = reinterpret_cast<const float*>(s_cand)[(i * kST + tid) * 4 + (r & 3)];
-          const uint4 br = s_beam[cb][i];
-          s_seg[wave][at++] = make_uint4(__float_as_uint(x), br.w + c, 0u, c != br.y ? 1u : 0u);
-        }
-      }
-      if (lane == 0) s_nseg[wave] = tot;
-    }
-    __syncthreads();  // B2: survivors
-
-    // ---- R. exact selection of the K best ----
-    const int n0 = s_nseg[0], n1 = s_nseg[1], n2 = s_nseg[2], n3 = s_nseg[3];
-    const int N = nlive + n0 + n1 + n2 + n3;
-    const bool fallback = s_ovf != 0 || N > 64;  // uniform
-    int nfin = 0;
-    if (fallback) {
-      // K rounds of "best key below the previous one" over every candidate
-      // (read back from LDS, rolled loops: a rare path kept small) and the
-      // blank candidates (wave 0).  A winner is named by its code: live
-      // position << 10 | label.
-      uint64_t prev = ~0ull;
-      for (int it = 0; it < K; ++it) {
-        uint64_t best = 0ull;
-        uint32_t wcode = 0u;
-#pragma unroll 1
-        for (int i = 0; i < kKmax; ++i) {
-          const float4 cv = s_cand[i * kST + tid];
-          const uint32_t sb = s_beam[cb][i].w;
-          const float xs[kLPL] = {cv.x, cv.y, cv.z, cv.w};
+        if (nent > 20) {  // uniform
 #pragma unroll
-          for (int j = 0; j < kLPL; ++j) {
-            const uint32_t c = static_cast<uint32_t>(tid + j * kST);
-            const uint64_t key = xs[j] != kNegInf ? order_key(xs[j], sb + c) : 0ull;
-            const bool better = key < prev && key > best;
-            best = better ? key : best;
-            wcode = better ? ((static_cast<uint32_t>(i) << 10) | c) : wcode;
+          for (int q = 5; q < 11; ++q) {
+            const float4 o = reinterpret_cast<const float4*>(s_x)[q];
+            r0 += o.x > x ? 1 : 0;
+            r1 += o.y > x ? 1 : 0;
+            r2 += o.z > x ? 1 : 0;
+            r3 += o.w > x ? 1 : 0;
           }
         }
-        if (wave == 0 && lane < nlive) {
-          const uint4 br = s_beam[cb][lane];
-          const float x = __uint_as_float(br.x) + dblank;
-          const uint64_t key = x != kNegInf ? order_key(x, br.w + static_cast<uint32_t>(V)) : 0ull;
-          const bool better = key < prev && key > best;
-          best = better ? key : best;
-          wcode = better ? ((static_cast<uint32_t>(lane) << 10) | 0x8000u) : wcode;  // blank of position lane
-        }
-        uint64_t wb = best;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const uint64_t o = __shfl_xor(wb, off);
-          wb = o > wb ? o : wb;
-        }
-        if (lane == 0) s_red[it & 1][wave] = wb;
-        __syncthreads();
-        uint64_t gb = s_red[it & 1][0];
-#pragma unroll
-        for (int w = 1; w < kSW; ++w) gb = s_red[it & 1][w] > gb ? s_red[it & 1][w] : gb;
-        if (gb == 0ull) break;  // nothing finite left (uniform)
-        if (best == gb && best != 0ull) {
-          const uint32_t i = (wcode >> 10) & 7u;
-          const uint4 br = s_beam[cb][i];
-          uint4 win;
-          if (wcode & 0x8000u) {
-            win = make_uint4(__float_as_uint(__uint_as_float(br.x) + dblank), br.w + static_cast<uint32_t>(V), 0u, 0u);
-          } else {
-            const uint32_t c = wcode & 1023u;
-            const float x = reinterpret_cast<const float*>(s_cand)[(i * kST + (c & 255u)) * 4u + (c >> 8)];
-            win = make_uint4(__float_as_uint(x), br.w + c, 0u, 0u);
-          }
-          s_win[it] = win;
-        }
-        prev = gb;
-        ++nfin;
-      }
-      __syncthreads();  // s_win complete
-    }
-
-    if (wave == 0) {
-      // ---- entries (normal path): lane l < nlive the blank candidate of live
-      // position l, then the four survivor segments ----
-      float ex = kNegInf;
-      uint32_t eidx = 0xFFFFFFFFu;
-      if (!fallback) {
-        if (lane < nlive) {
-          const uint4 br = s_beam[cb][lane];
-          ex = __uint_as_float(br.x) + dblank;
-          eidx = br.w + static_cast<uint32_t>(V);
-        } else if (lane < N) {
-          int e = lane - nlive, w = 0;
-          if (e >= n0) { e -= n0; w = 1; if (e >= n1) { e -= n1; w = 2; if (e >= n2) { e -= n2; w = 3; } } }
-          const uint4 v = s_seg[w][e];
-          ex = __uint_as_float(v.x);
-          eidx = v.y;
-        }
-      } else if (lane < nfin) {
-        const uint4 v = s_win[lane];
-        ex = __uint_as_float(v.x);
-        eidx = v.y;
-      }
-      const bool evalid = ex != kNegInf;
-      // parent slot, label, emission
-      const uint32_t epar = evalid ? eidx / static_cast<uint32_t>(W) : 0u;
-      const int ec = evalid ? static_cast<int>(eidx - epar * static_cast<uint32_t>(W)) : V;
-      const int elast = __builtin_amdgcn_ds_bpermute(static_cast<int>(epar) << 2, last);
-      const bool eemit = evalid && ec != V && ec != elast;
-      int src = lane;  // entry lane of winner `lane`
-      if (!fallback) {
-        // rank: the entries' keys counted from broadcast LDS reads, two at a
-        // time (lanes past N hold key 0)
-        const uint64_t key = evalid ? order_key(ex, eidx) : 0ull;
-        s_key[lane] = key;
-        int rank = 0;
-        const int N2 = (N + 1) >> 1;
-#pragma unroll 4
-        for (int m2 = 0; m2 < N2; ++m2) {  // uniform trip count
-          const ulonglong2 kk = reinterpret_cast<const ulonglong2*>(s_key)[m2];
-          rank += (kk.x > key ? 1 : 0) + (kk.y > key ? 1 : 0);
-        }
-        nfin = min(K, static_cast<int>(__popcll(__ballot(evalid))));
+        int rank = (r0 + r1) + (r2 + r3);
+        int nfin = min(K, static_cast<int>(__popcll(__ballot(evalid))));
         // winner of rank r learns its entry lane (others write to lane 63,
         // which no winner reads: K <= 8)
-        const int dst = (evalid && rank < K) ? rank : 63;
-        src = __builtin_amdgcn_ds_permute(dst << 2, lane);
+        bool top = evalid && rank < K;
+        int got = __builtin_amdgcn_ds_permute((top ? rank : 63) << 2, lane + 1);
+        // equal scores leave a rank without an entry or put more than K there
+        bool slow = __ballot(lane < nfin && got == 0) != 0ull || static_cast<int>(__popcll(__ballot(top))) != nfin;
+        const int epk = ei | (c << 3) | ((k_emit ? 1 : 0) << 14) | (static_cast<int>(br.z) << 15);
+        float wx = __int_as_float(__builtin_amdgcn_ds_bpermute((got - 1) << 2, __float_as_int(x)));
+        int pk = __builtin_amdgcn_ds_bpermute((got - 1) << 2, epk);
+        const float xk = rdlane(wx, K - 1);  // the K-th best (with K of them)
+        slow = slow || (nfin == K && __ballot(xo != kNegInf && xo >= xk) != 0ull);
+        if (slow) {  // uniform, rare
+          const uint64_t key = evalid ? order_key(x, static_cast<uint32_t>(ei * W + c)) : 0ull;
+          s_key[lane] = key;
+          wave_lds_fence();
+          rank = 0;
+          for (int m = 0; m < nent; ++m) rank += s_key[m] > key ? 1 : 0;
+          top = evalid && rank < K;
+          got = __builtin_amdgcn_ds_permute((top ? rank : 63) << 2, lane + 1);
+          wx = __int_as_float(__builtin_amdgcn_ds_bpermute((got - 1) << 2, __float_as_int(x)));
+          pk = __builtin_amdgcn_ds_bpermute((got - 1) << 2, epk);
+          const float xt = rdlane(wx, K - 1);
+          if (nfin == K && __ballot(xo != kNegInf && xo >= xt) != 0ull) {  // uniform
+            // candidates left out may equal the K-th best score: its places go
+            // to the lowest flat indices of all candidates with that score
+            const int ngt = static_cast<int>(__popcll(__ballot(evalid && x > xt)));
+            const int need = K - ngt;
+            int have = 0;
+            if (lane < kKmax) s_tie[lane] = static_cast<uint32_t>(V << 3);
+            wave_lds_fence();
+            for (int i = 0; i < K && have < need; ++i) {  // uniform
+              const uint4 bi = s_beam[i];
+              const float s = __uint_as_float(bi.x);
+              const int l0 = static_cast<int>(bi.y);
+              if (s == kNegInf) continue;  // dead position (uniform)
+              for (int c0 = 0; c0 <= V && have < need; c0 += 64) {
+                const int cc = c0 + lane;
+                float y = kNegInf;
+                if (cc <= V) {
+                  y = s + row[cc];
+                  if (cc < V && cc != l0) y = y + beta;
+                }
+                const uint64_t m = __ballot(y == xt);
+                const int at = have + static_cast<int>(__popcll(m & lanemask_lt()));
+                if (y == xt && at < need)
+                  s_tie[at] = static_cast<uint32_t>(i | (cc << 3) | ((cc < V && cc != l0 ? 1 : 0) << 14) |
+                                                    (static_cast<int>(bi.z) << 15));
+                have += static_cast<int>(__popcll(m));
+              }
+            }
+            wave_lds_fence();
+            if (lane >= ngt && lane < K) {
+              wx = xt;
+              pk = static_cast<int>(s_tie[lane - ngt]);
+            }
+          }
+        }
+        const bool valid = lane < nfin;
+        float xw = valid ? wx : kNegInf;
+        const int wc = (pk >> 3) & 2047;
+        const int par = (pk >> 15) & 7;
+        const bool emit = valid && ((pk >> 14) & 1);
+        // the label's value in the next frame of the batch
+        const float dn = (f + 1 < nf) ? row[kRow + min(wc, V)] : 0.0f;
+
+        // counters: the beams entering this frame
+        if (want_stats && lane < K && sc != kNegInf) st_alive += 1u;
+
+        // successor of the parent slot
+        const uint32_t plo = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(par << 2, static_cast<int>(hlo)));
+        const uint32_t phi = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(par << 2, static_cast<int>(hhi)));
+        const int plen = __builtin_amdgcn_ds_bpermute(par << 2, len);
+        // prune (Algorithm 1: below best - theta -> -inf)
+        const float lim = rdlane(xw, 0) - p.theta;
+        uint64_t h = (static_cast<uint64_t>(phi) << 32) | plo;
+        const uint64_t hm = mix_token(h, static_cast<uint32_t>(wc));
+        h = emit ? hm : h;
+        const int nlen = plen + (emit ? 1 : 0);
+        const int nlast = valid ? wc : V;
+        if (valid && xw < lim) xw = kNegInf;
+        if (want_stats && xw != kNegInf && emit) st_emit += 1u;
+        // recombination: same transcript hash, length and ends-in-blank flag as
+        // a live lower slot (slots in lanes 0..7 of one 16-lane row)
+        const bool alive0 = valid && xw != kNegInf;
+        const uint32_t meta = (static_cast<uint32_t>(nlen) & 0x3FFFFFFFu) | ((nlast == V ? 1u : 0u) << 30);
+        uint64_t rkey = h ^ (static_cast<uint64_t>(meta + 1u) * 0xD6E8FEB86659FD93ull);
+        if (!alive0) rkey = ~0ull;
+        const bool dup = detail::recomb_shifts<1, 7>(static_cast<uint32_t>(rkey), static_cast<uint32_t>(rkey >> 32)) && alive0;
+        const bool alive = alive0 && !dup;
+        if (lane < K) s_bp[n & 1][f * K + lane] = valid ? ((par << 16) | wc) : -1;
+
+        // the beam after this frame
+        sc = alive ? xw : kNegInf;
+        last = nlast;
+        len = nlen;
+        hlo = static_cast<uint32_t>(h);
+        hhi = static_cast<uint32_t>(h >> 32);
+        // as the next frame's scoring sees it: the live slots first, the
+        // other positions score -inf
+        const uint64_t am = __ballot(alive && lane < K);
+        const int na = static_cast<int>(__popcll(am));
+        const int below = static_cast<int>(__popcll(am & lanemask_lt()));
+        const bool liv = alive && lane < K;
+        if (lane < kKmax)
+          s_beam[liv ? below : na + lane - below] =
+              make_uint4(__float_as_uint(liv ? sc : kNegInf), static_cast<uint32_t>(liv ? last : V),
+                         static_cast<uint32_t>(lane), __float_as_uint(dn));
       }
-      // cross-lane reads run with every lane active (a source lane that is
-      // inactive reads as 0), so none sits in a short-circuit operand
-      const bool valid = lane < nfin;
-      float x = __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(ex)));
-      const int pk = __builtin_amdgcn_ds_bpermute(src << 2, static_cast<int>(epar & 7u) | (ec << 3) | ((eemit ? 1 : 0) << 14));
-      const int par = pk & 7;
-      const int c = (pk >> 3) & 2047;
-      const bool emit = valid && ((pk >> 14) & 1);
-      if (!valid) x = kNegInf;
-
-      // counters: the beams entering this frame
-      if (want_stats && lane < K && sc != kNegInf) st_alive += 1u;
-
-      // successor of the parent slot (its record, from LDS)
-      uint32_t prec[kSlotWords];
-#pragma unroll
-      for (int w4 = 0; w4 < kSlotWords; w4 += 4) {
-        const uint4 v = *reinterpret_cast<const uint4*>(&s_slot[par][w4]);
-        prec[w4] = v.x;
-        prec[w4 + 1] = v.y;
-        prec[w4 + 2] = v.z;
-        prec[w4 + 3] = v.w;
-      }
-      const uint32_t plo = prec[0], phi = prec[1];
-      const int plen = static_cast<int>(prec[2]);
-      uint64_t h = (static_cast<uint64_t>(phi) << 32) | plo;
-      const uint64_t hm = mix_token(h, static_cast<uint32_t>(c));
-      h = emit ? hm : h;
-      const int nlen = plen + (emit ? 1 : 0);
-      const int nlast = valid ? c : V;
-
-      // prune (Algorithm 1: below best - theta -> -inf)
-      const float lim = rdlane(x, 0) - p.theta;
-      if (valid && x < lim) x = kNegInf;
-      if (want_stats && x != kNegInf && emit) st_emit += 1u;
-      // recombination: same transcript hash, length and ends-in-blank flag as
-      // a live lower slot (slots in lanes 0..7 of one 16-lane row)
-      const bool alive0 = valid && x != kNegInf;
-      const uint32_t meta = (static_cast<uint32_t>(nlen) & 0x3FFFFFFFu) | ((nlast == V ? 1u : 0u) << 30);
-      uint64_t rkey = h ^ (static_cast<uint64_t>(meta + 1u) * 0xD6E8FEB86659FD93ull);
-      if (!alive0) rkey = ~0ull;
-      const bool dup = detail::recomb_shifts<1, 7>(static_cast<uint32_t>(rkey), static_cast<uint32_t>(rkey >> 32)) && alive0;
-      const bool alive = alive0 && !dup;
-      if (lane < K) bpb[static_cast<size_t>(t) * K + lane] = valid ? ((par << 16) | c) : -1;
-
-      // the beam after this frame
-      sc = alive ? x : kNegInf;
-      last = nlast;
-      len = nlen;
-      hlo = static_cast<uint32_t>(h);
-      hhi = static_cast<uint32_t>(h >> 32);
-      if (lane < K) *reinterpret_cast<uint4*>(&s_slot[lane][0]) = make_uint4(hlo, hhi, static_cast<uint32_t>(len), 0u);
-      const uint64_t am = __ballot(alive && lane < K);
-      // the beam as the next frame's scoring sees it (positions past the
-      // live slots score -inf)
-      const int na = static_cast<int>(__popcll(am));
-      if (alive && lane < K) {
-        const int lp = static_cast<int>(__popcll(am & lanemask_lt()));
-        s_beam[cb ^ 1][lp] = make_uint4(__float_as_uint(sc), static_cast<uint32_t>(last), 0u,
-                                        static_cast<uint32_t>(lane * W));
-      }
-      if (lane >= na && lane < kKmax)
-        s_beam[cb ^ 1][lane] = make_uint4(__float_as_uint(kNegInf), static_cast<uint32_t>(V), 0u, 0u);
-      if (lane == 0) s_nlive = na;
     }
-    __syncthreads();  // B3: beam table
+    lds_barrier();
   }
+  if (nbatch > 0) store_bp(nbatch - 1);
+  __syncthreads();
 
   // ---- the order of the final hypotheses (wave 0) ----
   const bool nbest = p.nbest_scores != nullptr;
@@ -493,8 +533,8 @@ __global__ void __launch_bounds__(kST) small_kernel(KernelParams p) {
   // walks live slot k into the row of its rank
   const bool walker = wave == 0 && (nbest ? (lane < K && sc != kNegInf) : (lane == 0 && have));
   if (have && L > 0) {
-    uint32_t* stg = reinterpret_cast<uint32_t*>(s_big);
-    const int tile_frames = (kStage * 2) / K;
+    uint32_t* stg = s_big;
+    const int tile_frames = kStageWords / K;
     int jb = nbest ? lane : best, cnext = -1, pos = 0;
     int32_t* orow = nullptr;
     if (walker) {
@@ -535,24 +575,28 @@ __global__ void __launch_bounds__(kST) small_kernel(KernelParams p) {
   }
 }
 
+template <int NJ>
 hipError_t launch(const KernelParams& p, hipStream_t s) {
-  hipLaunchKernelGGL(small_kernel, dim3(p.B), dim3(kST), 0, s, p);
+  hipLaunchKernelGGL(small_kernel<NJ>, dim3(p.B), dim3(kST), 0, s, p);
   return hipGetLastError();
 }
 
 }  // namespace small
 
-// The small-beam decoder serves beams of at most 8 without an LM or boosting,
-// where it is faster than the general one (1.45 vs 1.72 ms at K = 8 and 1.25
-// vs 1.67 ms at K = 4 on 32 utterances of 400 frames, V = 1024).  A form with
-// LM rows kept in LDS and the update in one wave lost to the general decoder
-// (2.46 vs 2.07 ms on the 3-gram workload at K = 8) and was removed.
+// The small-beam decoder serves beams of at most 8 without an LM or boosting:
+// the entries of K = 8 fill one wave's lanes, and a label's order in every beam
+// is its order in D only where no model adds to it (0.68 against 1.72 ms in
+// the general decoder at K = 8 on 32 utterances of 400 frames, V = 1024).
 bool small_beam_eligible(const KernelParams& p) {
   if (p.bt_nodes != nullptr || p.lm_states != nullptr || p.lm_arcs != nullptr) return false;
   if (p.K > small::kKmax || p.V > small::kVmax) return false;
   return (p.flags & (kFlagNoRowCache | kFlagLogSumExp | kFlagRepeatScore)) == 0;
 }
 
-hipError_t launch_small(const KernelParams& p, hipStream_t s) { return small::launch(p, s); }
+hipError_t launch_small(const KernelParams& p, hipStream_t s) {
+  if (p.V <= 64) return small::launch<1>(p, s);
+  if (p.V <= 256) return small::launch<4>(p, s);
+  return small::launch<16>(p, s);
+}
 
 }  // namespace ctcbeam
