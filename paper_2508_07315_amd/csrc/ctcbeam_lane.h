@@ -124,6 +124,13 @@ __device__ __forceinline__ float xor_lane(float v, int j, int lane) {
   return __uint_as_float(xor_lane(__float_as_uint(v), j, lane));
 }
 
+// barrier for LDS data: global loads issued before it stay in flight over it
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // inclusive prefix sum over the wave
 __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
   v += static_cast<int>(dpp_mov<kDppRowShr1>(static_cast<uint32_t>(v)));

@@ -11,8 +11,10 @@ Prints, per phase of the frame step (beam search: fill, barrier A,
 candidates, barrier B, bound, filter, barrier C, rank, barrier D, and the update
 as prune + recombination, new state, chunk plan and the rest; the class
 decoder, which serves beams over one chunk: plan, fill, barrier A, scoring,
-barrier B, bound, expansion, barrier C, rank, barrier D, update; greedy:
-scoring, the wave's best, the exchange barrier, the decision, chain headers +
+barrier B, bound, expansion, barrier C, rank, barrier D, update; the small-beam
+decoder, K <= 8 without models, its decoding wave: entries, rank, winners, equal
+scores, successors, recombination, new beam, the batch's barrier, read-out;
+greedy: scoring, the wave's best, the exchange barrier, the decision, chain headers +
 fold, continuations, log-prob row loads), the mean cycles per frame of each
 wave, averaged over the utterances (weighted by their frames), and the mean
 chunks (passes, refills) per frame.  Inputs are the seeded workloads of ``workloads``.
@@ -33,6 +35,7 @@ PHASES = {"beam": [(0, "fill"), (1, "bar A"), (2, "cand"), (3, "bar B"), (14, "b
                    (8, "upd rest")],
           "class": [(13, "plan"), (0, "fill"), (1, "bar A"), (2, "cand"), (3, "bar B"), (14, "bound"),
                     (4, "expand"), (5, "bar C"), (6, "rank"), (7, "bar D"), (8, "update")],
+          "small": list(enumerate(["entries", "rank", "winners", "ties", "succ", "recomb", "beam", "barrier", "tail"])),
           "greedy": list(enumerate(["score", "best", "barrier", "decide", "hdr+fold", "arcs", "rows"]))}
 WAVES = 8
 WORDS = 20
@@ -88,7 +91,9 @@ def main(argv=None):
     chunks = ph[:, 0, 10]
     nf = frames.sum()
     kind = "class" if args.mode == "beam" and ph[:, :, 19].sum() > 0 else args.mode
-    what = {"greedy": "refills", "class": "passes", "beam": "chunks"}[kind]
+    if kind == "beam" and lm is None and bt is None and w.K <= 8 and w.V <= 1024:
+        kind = "small"
+    what = {"small": "frames with equal scores", "greedy": "refills", "class": "passes", "beam": "chunks"}[kind]
     print(f"{w.name} {args.mode} K={1 if args.mode == 'greedy' else w.K} theta={theta}: {int(nf)} frames, "
           f"{chunks.sum() / max(nf, 1):.2f} {what}/frame")
     print("cycles per frame by wave (mean over utterances, weighted by frames)")
