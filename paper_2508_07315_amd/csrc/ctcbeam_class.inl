@@ -141,6 +141,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
   // classes a wave scores at once, CG of them with their row loads in flight
   constexpr int NCC = LPT <= 2 ? 16 : 32 / LPT;
   constexpr int kPass = 16;          // classes a pass takes
+  static_assert(kHot - kPass > KMX && kPool > KMX, "an overflow leaves more than K candidates");
   constexpr int kFG = NL <= 4 ? 16 : 8;  // new LM rows in the fill's segment table, 64 / kFG lanes each
   constexpr int CG = LPT <= 4 ? 8 / LPT : 1;
   constexpr int RW = 8;
@@ -152,8 +153,8 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
   constexpr int kLabels = LPT * kCT;
   constexpr int TU = 6;              // arc tiles of 64 in flight per wave
   constexpr int kBpFrames = SPL == 1 ? 8 : 4;  // frames of back-pointers kept in LDS
-  constexpr int kFixed = 1024 + KMX * 6 + kCW * 512 + 128 * 4 + kPool * 16 + kCW * kHot * 4 + 2 * KMX * RW * 4 + kCW * kPairs * (PW > 0 ? PW : 1) * 4 +
-                         (kLabels + 64) * 4 + KMX * 8 * 4 + 2 * 64 * 4 + kBpFrames * KMX * 4 + 2048;
+  constexpr int kFixed = 1024 + KMX * 10 + kCW * 512 + 128 * 4 + kPool * 16 + kCW * kHot * 4 + 2 * KMX * RW * 4 + kCW * kPairs * (PW > 0 ? PW : 1) * 4 +
+                         (kLabels + 64) * 4 + KMX * 8 * 4 + 2 * 64 * 4 + kBpFrames * KMX * 4 + 2048 - KMX * 4;
   // rows of the LM states and boosting nodes; the traceback's tiles after the
   // last frame
   constexpr int kArea = kRows ? ((kLdsBytes - kFixed) & ~255) : 32 * 1024;
@@ -174,15 +175,16 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
   __shared__ uint8_t s_rowh[2][kCW][256];
   __shared__ uint32_t s_xrow[2][16], s_xkey[2][16], s_xpid[2][16];
   __shared__ uint32_t s_potB[32];
-  __shared__ uint32_t s_ctop[KMX];               // log-sum-exp: highest score of a class (ordered bits)
-  __shared__ uint8_t s_cid[KMX], s_cj[KMX];      // class of a leading slot, leading slot of a class
+  // log-sum-exp: order key (score, slot) of a class's best slot; the lengths
+  // and ranks of the final hypotheses after the last frame
+  __shared__ unsigned long long s_ctop[KMX];
+  __shared__ uint8_t s_cid[KMX], s_cj[KMX];      // class of a leading slot, best slot of a class
   __shared__ uint32_t s_hist[2][64];
   __shared__ int32_t s_bpf[kBpFrames * KMX];
   __shared__ uint64_t s_dup[8][SPL];
   __shared__ uint64_t s_key;
   __shared__ int32_t s_n, s_over, s_best, s_bestlen;
   __shared__ float s_bestscore;
-  __shared__ uint32_t s_len[KMX], s_rank[KMX];
   __shared__ unsigned long long s_st[6];
 
   const int tid = threadIdx.x;
@@ -298,7 +300,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
     s_hist[1][lane] = 0u;
     *reinterpret_cast<uint4*>(&s_cht[4 * lane]) = make_uint4(~0u, ~0u, ~0u, ~0u);
 #pragma unroll
-    for (int h = 0; h < SPL; ++h) s_ctop[lane + 64 * h] = 0u;
+    for (int h = 0; h < SPL; ++h) s_ctop[lane + 64 * h] = 0ull;
   }
   if (tid == 0) {
     uint32_t* r = s_rec[0];
@@ -440,7 +442,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
         if (lead[h]) {
           const int id = CT + below(m);
           s_cid[lane + 64 * h] = static_cast<uint8_t>(id);
-          s_cj[id] = static_cast<uint8_t>(lane + 64 * h);
+          if (!lse) s_cj[id] = static_cast<uint8_t>(lane + 64 * h);
         }
         CT += __popcll(m);
       }
@@ -450,14 +452,19 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
         smx[h] = lx[h];
       }
       if (lse) {
-        // slots are in score order, unless log-sum-exp merges raised some
+        // slots are in score order, unless log-sum-exp merges raised some: a
+        // class's best slot is its highest score's lowest slot
 #pragma unroll
         for (int h = 0; h < SPL; ++h)
-          if (alive[h]) atomicMax(&s_ctop[cls[h]], static_cast<uint32_t>(order_key(sc[h], 0u) >> 32));
+          if (alive[h])
+            atomicMax(&s_ctop[cls[h]], static_cast<unsigned long long>(order_key(sc[h], static_cast<uint32_t>(lane + 64 * h))));
 #pragma unroll
         for (int h = 0; h < SPL; ++h) {
-          const uint32_t u = alive[h] ? s_ctop[cls[h]] : 0u;
+          const uint64_t top = alive[h] ? s_ctop[cls[h]] : 0ull;
+          const uint32_t u = static_cast<uint32_t>(top >> 32);
           smx[h] = alive[h] ? __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u) : kNegInf;
+          if (alive[h] && ~static_cast<uint32_t>(top) == static_cast<uint32_t>(lane + 64 * h))
+            s_cj[cls[h]] = static_cast<uint8_t>(lane + 64 * h);
         }
       }
     }
@@ -507,7 +514,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
       uint32_t fl = 0u, fb = 0u;    // lane f: pair id | row << 16
       uint32_t flk = 0u, fbk = 0u;  // lane f: LM state / boosting node
       int C = min(CT - gbase, kPass);
-      // lane i < C: class gbase + i; its lowest slot, rows and highest score
+      // lane i < C: class gbase + i; its best slot, rows and highest score
       const int cJ = s_cj[gbase + min(lane, C - 1)];
       uint32_t cP = 0u;   // LM row | boosting row << 8
       float cS;
@@ -1041,8 +1048,10 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
                   }
                   bool hot = x >= tau;
                   if (kmode) {
-                    const uint32_t low = static_cast<uint32_t>(rdlane(cJ, c0 + q));
-                    hot = hot && order_key(x, (low << kSlotShift) | (rcc[jj] << kLabelShift)) >= kmin;
+                    // the key of the best slot's candidate: every pair that
+                    // passes has one, but for that slot's repeat
+                    const uint32_t bs = static_cast<uint32_t>(rdlane(cJ, c0 + q));
+                    hot = hot && order_key(x, (bs << kSlotShift) | (rcc[jj] << kLabelShift)) >= kmin;
                   }
                   const uint64_t m = __ballot(hot);
                   const int at = nh + below(m);
@@ -1147,7 +1156,9 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
           if (s_over == 0) break;  // uniform
           // Overflow: the K-th best of the entries that fit bounds the K-th
           // best candidate; keep what reaches it and expand this chunk
-          // again.  The bound rises each time, so this ends.
+          // again.  More than K entries fit (a full pool, or a wave's full
+          // list, of whose pairs at most kPass have no candidate), all of them
+          // at or above the last bound, so it rises each time and this ends.
           CTCBEAM_PHASE_COUNT(17);
           constexpr int EPT = kPool / kCT > 0 ? kPool / kCT : 1;  // entries a thread
           const int n = min(poff + s_n, kPool);
@@ -1219,7 +1230,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
       *reinterpret_cast<uint4*>(&s_cht[4 * lane]) = make_uint4(~0u, ~0u, ~0u, ~0u);
       if (lse) {
 #pragma unroll
-        for (int h = 0; h < SPL; ++h) s_ctop[lane + 64 * h] = 0u;
+        for (int h = 0; h < SPL; ++h) s_ctop[lane + 64 * h] = 0ull;
       }
     }
     const int N = min(poff + s_n, kPool);
@@ -1417,6 +1428,8 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
 
   // ---- LM.Final, order of the final hypotheses ----
   const bool nbest = p.nbest_scores != nullptr;
+  uint32_t* const s_len = reinterpret_cast<uint32_t*>(s_ctop);  // by rank
+  uint32_t* const s_rank = s_len + KMX;                         // by slot
   if (wave == 0) {
     float sj[SPL];
 #pragma unroll
@@ -1470,7 +1483,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
       if (nbest && js < K) {
         p.nbest_scores[static_cast<size_t>(b) * K + rank[h]] = sj[h];
         p.nbest_lengths[static_cast<size_t>(b) * K + rank[h]] = nlen;
-        s_len[rank[h]] = static_cast<uint32_t>(nlen);  // by rank
+        s_len[rank[h]] = static_cast<uint32_t>(nlen);
         s_rank[js] = static_cast<uint32_t>(rank[h]);
       }
     }

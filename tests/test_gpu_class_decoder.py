@@ -85,3 +85,41 @@ def test_ties_overflow_the_pool(V, K):
     r = oracle.decode(lp, lens, K, 0.0, 0.25, want_nbest=True)
     np.testing.assert_array_equal(tok.cpu().numpy(), r["nbest_tokens"])
     np.testing.assert_allclose(sc.cpu().numpy(), r["nbest_scores"], rtol=0, atol=1e-4)
+
+
+@pytest.mark.parametrize("V,K,phrases", [(1500, 12, False), (2000, 8, False), (2048, 16, False), (4096, 64, False),
+                                         (700, 20, True), (1024, 12, True), (1024, 100, True)])
+def test_ties_with_merged_best_slot(V, K, phrases):
+    """Log-sum-exp merges the two alignments of A above AC and C, which hold
+    the lower slots, so the class's best slot is not its lowest one.  Frames
+    of equal values then tie at the K-th best score for every label of that
+    slot: more than a wave's list of pairs.  The few better labels (and, with
+    phrases, the better label of another class, X) must not be cut off."""
+    import torch
+    B, T = 12, 5
+    rng = np.random.default_rng([V, K])
+    lp = (-6.0 - 2.0 * rng.random((B, T, V + 1))).astype(np.float32)
+    lp[:, 2:] = -8.0
+    off, toks = np.array([0, 2], dtype=np.int32), rng.choice(V, 2, replace=False).astype(np.int32)
+    w = 0.25 if phrases else 0.0
+    for b in range(B):
+        A, C = rng.choice(np.setdiff1d(np.arange(V), toks), 2, replace=False)
+        lp[b, 0, A] = lp[b, 0, V] = -0.7
+        lp[b, 1, A], lp[b, 1, C] = -1.0, -0.9
+        if phrases:
+            lp[b, 1, toks[0]] = -0.95 - w
+        for t in range(2, T):
+            c = rng.integers(V // 2, V, size=4)
+            lp[b, t, c] = -8.0 + rng.choice([0.5, 1.0, 2.0], size=4)
+    lens = np.full(B, T, dtype=np.int32)
+    log("ties with a merged best slot", V, K, phrases)
+    dev = device()
+    bt = P.ctcbeam_boost_build(V, off, toks) if phrases else None
+    tok, ln, sc, ws = P.ctcbeam_decode_nbest(torch.from_numpy(lp).to(dev), torch.from_numpy(lens).to(dev), K,
+                                             boost_w=w, boost=bt, logsumexp=True)
+    torch.cuda.synchronize()
+    r = oracle.decode(lp, lens, K, 0.0, 0.0, w, bt=oracle.BT(V, off, toks) if phrases else None,
+                      n_threads=oracle_threads(), want_nbest=True, logsumexp=True)
+    np.testing.assert_array_equal(tok.cpu().numpy(), r["nbest_tokens"])
+    np.testing.assert_allclose(sc.cpu().numpy(), r["nbest_scores"], rtol=0, atol=1e-4)
+    assert P.ctcbeam_query_status(ws) == 0
