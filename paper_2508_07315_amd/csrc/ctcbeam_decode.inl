@@ -90,8 +90,9 @@ constexpr uint32_t kTargetMask = (1u << 23) - 1u;
 // filled; an entry holds its arc's target state.
 // REP: the repeat-scoring variant (CTCBEAM_FLAG_REPEAT_SCORE), a kernel of
 // its own so that the default kernels carry none of its state.
-// Serves beams of one chunk (at most 16 / LPT) and, above 2048 tokens with an
-// LM, of at most 16; the class decoder serves the rest.
+// Serves beams of one chunk (at most 16 / LPT) and the beams of several chunks
+// (at most 16) that class_eligible leaves to it; the class decoder serves the
+// rest.
 template <int LPT, int NLEV, bool HAS_BT, bool SKIP, bool CACHE, bool REP>
 __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   constexpr int SPL = 1;                      // beam slots per lane
@@ -1983,34 +1984,38 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   }
 }
 
+// Whether class_eligible leaves beams of several chunks to this decoder at LPT
+// labels per lane, for an LM of NLEV levels (-1: none).
+constexpr bool multi_chunk(int LPT, int NLEV, bool boosting) {
+  if (LPT == 8) return NLEV >= 0 || boosting;
+  return LPT == 4 && boosting && (NLEV == 2 || NLEV == 3);
+}
+
 template <int LPT, int NLEV, bool SKIP, bool REP>
 hipError_t launch_skip(const KernelParams& p, hipStream_t s) {
   dim3 grid(p.B), block(kThreads);
   constexpr bool kCacheable = !SKIP && LPT >= 2 && NLEV > 0;
-  if constexpr (REP) {
-    // the repeat-scoring variant reads uncached rows; with neither an LM nor
-    // boosting it has nothing to repeat (the caller takes the default kernel)
-    if (p.bt_nodes != nullptr) {
-      hipLaunchKernelGGL((decode_kernel<LPT, NLEV, true, SKIP, false, true>), grid, block, 0, s, p);
-    } else {
-      if constexpr (NLEV < 0) return hipErrorInvalidValue;
-      else hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SKIP, false, true>), grid, block, 0, s, p);
-    }
-  } else if (p.bt_nodes != nullptr) {
-    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, true, SKIP, false, false>), grid, block, 0, s, p);
-  } else if (kCacheable && p.lm_states_below_2p23 && !(p.flags & kFlagNoRowCache)) {
-    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SKIP, kCacheable, false>), grid, block, 0, s, p);
+  // the repeat-scoring variant reads uncached rows; with neither an LM nor
+  // boosting it has nothing to repeat (the caller takes the default kernel)
+  constexpr bool kBoosted = !SKIP || multi_chunk(LPT, NLEV, true);
+  constexpr bool kPlain = !SKIP ? !REP || NLEV >= 0 : multi_chunk(LPT, NLEV, false);
+  if (p.bt_nodes != nullptr) {
+    if constexpr (!kBoosted) return hipErrorInvalidValue;
+    else hipLaunchKernelGGL((decode_kernel<LPT, NLEV, true, SKIP, false, REP>), grid, block, 0, s, p);
+  } else if constexpr (!kPlain) {
+    return hipErrorInvalidValue;
+  } else if (!REP && kCacheable && p.lm_states_below_2p23 && !(p.flags & kFlagNoRowCache)) {
+    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SKIP, !REP && kCacheable, REP>), grid, block, 0, s, p);
   } else {
-    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SKIP, false, false>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((decode_kernel<LPT, NLEV, false, SKIP, false, REP>), grid, block, 0, s, p);
   }
   return hipGetLastError();
 }
 
 template <int LPT, int NLEV, bool REP>
 hipError_t launch_nlev(const KernelParams& p, hipStream_t s) {
-  // beams of more than one chunk (16 / LPT rows) skip ranks; only the widest
-  // vocabularies, with an LM, take such beams here
-  if constexpr (LPT == 8 && NLEV >= 0) {
+  // beams of more than one chunk (16 / LPT rows) skip ranks
+  if constexpr (multi_chunk(LPT, NLEV, true) || multi_chunk(LPT, NLEV, false)) {
     if (p.K > 16 / LPT) return launch_skip<LPT, NLEV, true, REP>(p, s);
   }
   if (p.K > 16 / LPT) return hipErrorInvalidValue;

@@ -182,18 +182,34 @@ hipError_t launch_class_lpt8(const KernelParams& p, hipStream_t stream);
 
 // Whether the class decoder serves a beam search.  It scores V labels once per
 // class of beams instead of once per beam, but spends more dependent steps a
-// frame, so beams that fit one chunk of the general decoder stay there (K = 8,
-// 1024 tokens, 3-gram: 0.73 against 1.09 ms for 32 utterances of 120 frames)
-// except over character sets, whose few labels leave the general decoder's
-// bound too loose (45 tokens, K = 16: 1.53 against 0.94 ms).  Above one chunk it
-// is faster (1024 tokens, 3-gram: 1.37x at K = 16, 1.86x at K = 48; 11x without
-// models at 2500 tokens, K = 48) as long as a few LM rows fit its LDS: at 4000
-// tokens with an LM and K = 16 it takes 4.6 against 3.7 ms.
+// frame and keeps fewer LM rows in LDS the more tokens there are.  Figures:
+// general / class decoder time, 32 utterances of 250 frames, models counted in
+// synthetic text (shorter utterances favour the general decoder: 0.85 for 1.00
+// at 60 frames, 3000 tokens, 3-gram, K = 12).
+// - Beams of one chunk of the general decoder stay there (K = 8, 1024 tokens,
+//   3-gram: 0.67), except over character sets, whose few labels leave the
+//   general decoder's bound too loose (64 tokens, K = 9..16: 1.3..3.0; 10
+//   tokens 1.03..1.3; with phrases from about 144 candidates a frame: 8 tokens,
+//   K = 16 0.95..1.10, 16 tokens, K = 9 0.97..1.05).
+// - Above 16 beams it is faster throughout (17 beams 0.93..2.1, 24 beams
+//   0.98..1.9 with a 2-gram or higher and phrases at 1600 to 4096 tokens).
+// - Phrases alone: 1.1 and above, but for K = 3 and 4 over wide vocabularies
+//   (2560 tokens 0.97..1.03, 4096 tokens 0.87..0.92).
+// - LM and phrases: 1.08 and above from 2049 to 2560 tokens; at 4096 tokens
+//   0.75..0.95.  Just below 2048 tokens, where an LDS holds five LM rows and as
+//   many boosting rows, it loses for 3- and 4-grams at K = 7..16 (1900 to 2048
+//   tokens 0.90..1.04; 1800 tokens 1.03..1.16; other orders 0.96..1.3).
+// - LM alone: up to 3072 tokens 0.98..1.11, below 2-grams more, above 4-grams
+//   1.3; K = 3 0.96..1.00 for 2- to 4-grams; at 4096 tokens 0.72..0.95.
 inline bool class_eligible(const KernelParams& p) {
   const bool lm = p.lm_states != nullptr || p.lm_arcs != nullptr, bt = p.bt_nodes != nullptr;
   const int chunk = p.V <= 512 ? 16 : p.V <= 1024 ? 8 : p.V <= 2048 ? 4 : 2;
-  if (p.K <= chunk) return p.V <= 64 && p.K > 8;
-  return !lm || p.K > 16 || p.V <= (bt ? 2560 : 3072);
+  if (p.K <= chunk) return p.V <= 64 && p.K > 8 && (!bt || p.V * p.K >= 144);
+  if (p.K > 16) return true;
+  if (!lm) return !bt || p.K > 4 || p.V <= 2560;
+  if (!bt) return p.V <= 3072 && !(p.V > 2048 && p.K == 3 && p.lm_nlev >= 1 && p.lm_nlev <= 3);
+  if (p.V > 1800 && p.V <= 2048 && p.K > 6) return p.lm_nlev != 2 && p.lm_nlev != 3;
+  return p.V <= 2560;
 }
 
 inline hipError_t launch_decode(const KernelParams& p, hipStream_t stream) {

@@ -1,16 +1,18 @@
-"""GPU parity of fill groups: with beams over one chunk (K above 16 / labels
-per lane) and no row cache, beams in the same LM state read one LM row and
-beams with the same boosting list one boosting row, filled once for a group
-of consecutive chunks.  Sharing changes which rows are filled, never a score,
-so the results must equal the CPU oracle's (tokens bit-exact, scores within
-1e-4).
+"""GPU parity of beams over one chunk of the general decoder (K above 16 /
+labels per lane), whose beams share LM rows and boosting rows: the class
+decoder keeps a row per LM state and per boosting node; the general decoder,
+which serves the (5, 3000, 16) case here, reads one row per state and list,
+filled once for a group of consecutive chunks.  Sharing changes which rows are
+filled, never a score, so the results must equal the CPU oracle's (tokens
+bit-exact, scores within 1e-4).
 
 * 5- and 6-gram LMs of a few thousand n-grams (most hypotheses back off to
   short, shared states) with K = 9..128 (one and two beam slots per lane),
   vocabularies of 300, 400, 1024, 1500 and 3000 tokens (one, two, four and
   eight labels per lane), with and without boosting, theta = inf and 12,
-  1-best and N-best.  At 3000 tokens a group holds one boosting list, so an
-  LM state whose beams hold several lists is split over groups list by list;
+  1-best and N-best.  In the general decoder at 3000 tokens a group holds one
+  boosting list, so an LM state whose beams hold several lists is split over
+  groups list by list;
 * log-sum-exp recombination and repeat scoring on the same path;
 * a witness that the final beams do share LM states (the longest suffix of
   <s> + tokens that is an n-gram of the model), so that shared rows are what
@@ -75,7 +77,7 @@ def _lm_state(entries, order, bos, toks):
     (5, 1024, 16, False), (5, 1024, 64, True), (6, 1024, 40, True), (6, 1024, 64, False),
     (6, 1024, 9, True), (6, 300, 33, True), (5, 1500, 64, False), (5, 1500, 24, True),
     (6, 1024, 100, True), (5, 1024, 128, False), (6, 400, 77, True),
-    (5, 3000, 24, True), (5, 3000, 64, True)])
+    (5, 3000, 24, True), (5, 3000, 64, True), (5, 3000, 16, True)])
 def test_shared_rows(order, V, K, boost):
     w = _workload(order, V, K, boost, 31000 + 97 * order + K)
     lm, bt, olm, obt = handles(w)
@@ -151,12 +153,12 @@ def test_final_beams_share_lm_states():
 
 
 def test_wide_vocabulary_splits_states_over_groups():
-    # Witness for the (5, 3000, 64, boosting) case above: in some frames of
-    # the oracle's search the live beams of one LM state sit in two boosting
-    # states, more than a group holds at 3000 tokens (one list), so the plan
-    # splits that state over groups list by list.
+    # Witness for the (5, 3000, 16, boosting) case above, which the general
+    # decoder serves: in some frames of the oracle's search the live beams of
+    # one LM state sit in two boosting states, more than a group holds at 3000
+    # tokens (one list), so the plan splits that state over groups list by list.
     import collections
-    order, V, K = 5, 3000, 64
+    order, V, K = 5, 3000, 16
     w = _workload(order, V, K, True, 31000 + 97 * order + K)
     olm, obt = oracle_lm(w.lm, w.V), oracle_bt(w.boost, w.V)
     lp = W.make_logprobs(w)
