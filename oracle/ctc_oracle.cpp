@@ -423,6 +423,9 @@ void decode_one(const DecodeArgs& a, int b) {
       hyp[k].s = hyp[k].s + wb;
     }
   }
+  // A NaN score counts as -inf.
+  for (int k = 0; k < K; ++k)
+    if (std::isnan(hyp[k].s)) hyp[k].s = NEG_INF;
   int best = 0;
   for (int k = 1; k < K; ++k)
     if (hyp[k].s > hyp[best].s) best = k;

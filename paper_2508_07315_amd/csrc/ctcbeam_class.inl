@@ -1437,8 +1437,10 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
   const bool nbest = p.nbest_scores != nullptr;
   uint32_t* const s_len = reinterpret_cast<uint32_t*>(s_ctop);  // by rank
   uint32_t* const s_rank = s_len + KMX;                         // by slot
+  float sj[SPL];  // wave 0: final score of the slot, -inf for a dead one
+#pragma unroll
+  for (int h = 0; h < SPL; ++h) sj[h] = kNegInf;
   if (wave == 0) {
-    float sj[SPL];
 #pragma unroll
     for (int h = 0; h < SPL; ++h) {
       const int js = lane + 64 * h;
@@ -1464,9 +1466,10 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
         const float wb = boost_w * static_cast<float>(-static_cast<int>(p.bt_nodes[bts[h]].pot & 0xFFu));
         s = s + wb;
       }
-      sj[h] = (js < K) ? s : kNegInf;
+      sj[h] = (js < K && s > kNegInf) ? s : kNegInf;
     }
-    // rank of each slot: final score descending, lowest slot on ties
+    // rank of each slot: final score descending, lowest slot on ties (a NaN
+    // would leave ranks without a slot)
     int rank[SPL];
 #pragma unroll
     for (int h = 0; h < SPL; ++h) rank[h] = 0;
@@ -1532,9 +1535,8 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
 
   // ---- traceback through the back-pointers, staged in LDS tiles ----
   // 1-best: lane 0 of wave 0 walks the best slot.  N-best: lane j of wave 0
-  // walks slots j + 64 h (every live slot) and writes the rows of their ranks.
-  // (the LM.Final term is finite, so some slot is live exactly when the best
-  // final score is finite)
+  // walks slots j + 64 h (every slot with a final score) and writes the rows of
+  // their ranks.
   if (have && L > 0) {
     int32_t* const s_bp = reinterpret_cast<int32_t*>(s_area);
     const int tile_frames = kArea / 4 / K;
@@ -1544,7 +1546,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
 #pragma unroll
     for (int h = 0; h < SPL; ++h) {
       const int js = lane + 64 * h;
-      walker[h] = (wave == 0) && (nbest ? (js < K && sc[h] != kNegInf) : (h == 0 && lane == 0));
+      walker[h] = (wave == 0) && (nbest ? sj[h] != kNegInf : (h == 0 && lane == 0));
       jb[h] = nbest ? js : best;
       cnext[h] = -1;
       orow[h] = nullptr;

@@ -1841,6 +1841,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
 
   // ---- LM.Final, order of the final hypotheses ----
   const bool nbest = p.nbest_scores != nullptr;
+  float fin = kNegInf;  // wave 0: final score of the slot, -inf for a dead one
   if (wave == 0) {
     float s = sc[0];
     if (HAS_LM && j < K && s != kNegInf) {
@@ -1877,8 +1878,10 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       const float wb = boost_w * static_cast<float>(-btpot[0]);
       s = s + wb;
     }
-    // rank of each slot: final score descending, lowest slot on ties
-    const float sj = (j < K) ? s : kNegInf;
+    // rank of each slot: final score descending, lowest slot on ties (a NaN
+    // would leave ranks without a slot)
+    const float sj = (j < K && s > kNegInf) ? s : kNegInf;
+    fin = sj;
     int rank = 0;
     for (int i = 0; i < K; ++i) {
       const float si = rdlane(sj, i);
@@ -1933,10 +1936,9 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
 
   // ---- traceback through the back-pointers, staged in LDS tiles ----
   // 1-best: lane 0 of wave 0 walks the best slot.  N-best: lane j of wave 0
-  // walks slot j (every live slot) and writes the row of its rank.
-  // (the LM.Final term is finite, so some slot is live exactly when the best
-  // final score is finite)
-  const bool walker = (wave == 0) && (nbest ? (j < K && sc[0] != kNegInf) : (lane == 0 && have));
+  // walks slot j (every slot with a final score) and writes the row of its
+  // rank.
+  const bool walker = (wave == 0) && (nbest ? fin != kNegInf : (lane == 0 && have));
   if (have && L > 0) {
     const int tile_frames = kBigWords / K;
     int jb = nbest ? j : best, cnext = -1;

@@ -531,7 +531,7 @@ __global__ void __launch_bounds__(64 * NW) greedy_kernel(KernelParams p) {
     const float wb = boost_w * static_cast<float>(-pot);
     s = s + wb;
   }
-  if (dead) {
+  if (dead || !(s > kNegInf)) {  // (LM.Final may end a hypothesis: -inf, or NaN from 0 * -inf)
     s = kNegInf;
     nout = 0;
   }

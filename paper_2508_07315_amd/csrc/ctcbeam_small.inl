@@ -519,10 +519,11 @@ __global__ void __launch_bounds__(kST) small_kernel(KernelParams p) {
 
   // ---- the order of the final hypotheses (wave 0) ----
   const bool nbest = p.nbest_scores != nullptr;
+  // (without models the final score is the beam's; -inf for a dead slot)
+  const float sj = (lane < K && sc > kNegInf) ? sc : kNegInf;
   if (wave == 0) {
-    const float s = sc;
-    const float sj = lane < K ? s : kNegInf;
-    // rank: final score descending, lowest slot on ties
+    // rank: final score descending, lowest slot on ties (a NaN would leave
+    // ranks without a slot)
     int rank = 0;
     for (int i = 0; i < K; ++i) {
       const float si = rdlane(sj, i);
@@ -586,7 +587,7 @@ __global__ void __launch_bounds__(kST) small_kernel(KernelParams p) {
   // ---- traceback through the back-pointers, staged in LDS tiles ----
   // 1-best: lane 0 of wave 0 walks the best slot; N-best: lane k of wave 0
   // walks live slot k into the row of its rank
-  const bool walker = wave == 0 && (nbest ? (lane < K && sc != kNegInf) : (lane == 0 && have));
+  const bool walker = wave == 0 && (nbest ? sj != kNegInf : (lane == 0 && have));
   if (have && L > 0) {
     uint32_t* stg = s_big;
     const int tile_frames = kStageWords / K;
