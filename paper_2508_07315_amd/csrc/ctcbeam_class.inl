@@ -232,15 +232,14 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
   int RL = 0, RB = 0;
   {
     if (HAS_LM && HAS_BT) {
-      // Boosting rows cost half an LM row, and somewhat fewer nodes than
-      // states are live: three tenths of the area and what is left over after
-      // the LM rows (2048 tokens, 3-gram and 1000 phrases, five rows of each
-      // instead of six and three: 1.07x at K = 16, 1.12x at K = 64; 1024
-      // tokens, K = 64: 1.04x of a quarter; a third is slower below 1024).  A
-      // quarter while the rows hold about a pass of states (1024 tokens,
-      // K = 16, 4- and 6-gram: 1.004x and 1.007x).
+      // Boosting rows cost half an LM row, and fewer nodes than states are
+      // live: a quarter of the area, three tenths where rows are scarce (2048
+      // tokens, 3-gram and 1000 phrases, five rows of each instead of six and
+      // three: 1.07x at K = 16, 1.12x at K = 64; but 1024 tokens, K = 16:
+      // 0.993x, 930 tokens, 34 phrases, K = 70: 0.98x), and what is left over
+      // after the LM rows.
       const int q = area / (4 * VS);     // rows of 4 bytes a label
-      RB = max(q >= 4 ? 2 : 1, K <= kPass && q >= 24 ? q / 4 : 3 * q / 10);
+      RB = max(q >= 4 ? 2 : 1, q >= 24 ? q / 4 : 3 * q / 10);
       RL = min(32, (q - RB) / 2);
       RB = min(32, q - 2 * RL);
     } else if (HAS_LM) {
