@@ -175,8 +175,8 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
   __shared__ uint8_t s_rowh[2][kCW][256];
   __shared__ uint32_t s_xrow[2][16], s_xkey[2][16], s_xpid[2][16];
   __shared__ uint32_t s_potB[32];
-  // log-sum-exp: order key (score, slot) of a class's best slot; the lengths
-  // and ranks of the final hypotheses after the last frame
+  // log-sum-exp: order key (score, slot) of a class's best slot where that is
+  // not its lowest one, else 0; the lengths and ranks of the final hypotheses after the last frame
   __shared__ unsigned long long s_ctop[KMX];
   __shared__ uint8_t s_cid[KMX], s_cj[KMX];      // class of a leading slot, best slot of a class
   __shared__ uint32_t s_hist[2][64];
@@ -459,17 +459,19 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
       }
       if (lse) {
         // slots are in score order, unless log-sum-exp merges raised some: a
-        // class's best slot is its highest score's lowest slot
+        // class's best slot is its highest score's lowest slot.  Only slots
+        // above their leading slot's score compete (few; one address takes
+        // its atomics one after the other)
 #pragma unroll
         for (int h = 0; h < SPL; ++h)
-          if (alive[h])
+          if (alive[h] && sc[h] > lx[h])
             atomicMax(&s_ctop[cls[h]], static_cast<unsigned long long>(order_key(sc[h], static_cast<uint32_t>(lane + 64 * h))));
 #pragma unroll
         for (int h = 0; h < SPL; ++h) {
-          const uint64_t top = alive[h] ? s_ctop[cls[h]] : 0ull;
+          const uint64_t top = alive[h] ? s_ctop[cls[h]] : 0ull;  // 0: the leading slot
           const uint32_t u = static_cast<uint32_t>(top >> 32);
-          smx[h] = alive[h] ? __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u) : kNegInf;
-          if (alive[h] && ~static_cast<uint32_t>(top) == static_cast<uint32_t>(lane + 64 * h))
+          smx[h] = top != 0ull ? __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u) : lx[h];
+          if (top != 0ull ? ~static_cast<uint32_t>(top) == static_cast<uint32_t>(lane + 64 * h) : lead[h])
             s_cj[cls[h]] = static_cast<uint8_t>(lane + 64 * h);
         }
       }
