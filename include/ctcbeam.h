@@ -27,7 +27,9 @@
  *       x = s_k + D[t][c]; if c is neither blank nor a repeat:
  *       x = x + beta; x = x + fl(alpha * LM); x = x + fl(boost_w * BT);
  *   - TopK keeps the K best by (score descending, flat index k*W + c
- *     ascending); candidates at -inf are never kept as live beams;
+ *     ascending); candidates at -inf are never kept as live beams; a NaN
+ *     score (of a candidate, or of a hypothesis after LM.Final) counts as
+ *     -inf, for tokens, repeats and blanks alike;
  *   - pruning: a kept score below (best kept score - theta) becomes -inf;
  *   - recombination keeps the first (best) of the beams that share the
  *     collapsed transcript and whether they end in blank; the others become

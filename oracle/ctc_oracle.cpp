@@ -262,7 +262,7 @@ float lse32(float a, float b) {
   if (a < b) std::swap(a, b);
   if (b == NEG_INF) return a;
   const float d = b - a;
-  if (d < -80.0f) return a;
+  if (!(d >= -80.0f)) return a;  // (NaN: both +inf)
   const float e = exp32_nonpos(d);
   const float l = (e < 5.9604645e-8f) ? e : log1p32_unit(e);
   return a + l;
@@ -342,7 +342,9 @@ void decode_one(const DecodeArgs& a, int b) {
             x = x + wb;
           }
         }
-        // a dead beam stays -inf whatever is added to it
+        // a dead beam stays -inf whatever is added to it; a NaN score counts
+        // as -inf
+        if (!alive || std::isnan(x)) x = NEG_INF;
         cand[static_cast<size_t>(k) * W + c] = Cand{x, static_cast<int64_t>(k) * W + c};
       }
     }

@@ -79,6 +79,7 @@ using detail::kNegInf;
 using detail::lane_in;
 using detail::lse32;
 using detail::mix_token;
+using detail::no_nan;
 using detail::order_key;
 using detail::rdlane;
 using detail::recomb_shifts;
@@ -376,7 +377,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
 #pragma unroll
     for (int h = 0; h < SPL; ++h) {
       na += __popcll(__ballot(alive[h]));
-      xblank[h] = sc[h] + rBlank;
+      xblank[h] = no_nan(sc[h] + rBlank);
       if (lane + 64 * h < K) tb = fminf(tb, xblank[h]);
     }
     const bool full = na == K;  // uniform

@@ -1206,7 +1206,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       if (ch == 0 && wave == 0 && lane < K) {
         // blank candidates of every slot into the reserved region
         const float x = sc[0] + rBlank;
-        const bool ok = sc[0] != kNegInf && x != kNegInf;
+        const bool ok = x > kNegInf;  // (a NaN is no candidate)
         s_res[mpar][j] = make_uint4(__float_as_uint(ok ? x : kNegInf),
                                     ok ? static_cast<uint32_t>(j * W + V) : 0xFFFFFFFFu, 0u, 0u);
       }
@@ -1244,7 +1244,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
         float m1 = fmaxf(b2 ? m2[1] : m2[0], xor_lane(b2 ? m2[0] : m2[1], 4, lane));
         m1 = fmaxf(m1, xor_lane(m1, 8, lane));
         m1 = fmaxf(m1, xor_lane(m1, 16, lane));
-        m1 = fmaxf(m1, xor_lane(m1, 32, lane));
+        m1 = no_nan(fmaxf(m1, xor_lane(m1, 32, lane)));  // (a group of NaN candidates only)
         if (lane < 8) s_top[wave * 8 + lane] = m1;
         if (kSmallK || (kMaySmallK && K <= 8)) {
           float wm = fmaxf(m1, xor_lane(m1, 1, lane));
@@ -1257,10 +1257,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       // score also bounds the K-th best from below (registers only: small
       // beams take it before the barrier)
       const auto blank_bound = [&]() __attribute__((always_inline)) {
-        float tb = (lane < K) ? sc[0] + rBlank : __builtin_huge_valf();
-#pragma unroll
-        for (int h = 1; h < SPL; ++h)
-          if (j + 64 * h < K) tb = fmin_sel(tb, sc[h] + rBlank);
+        float tb = (lane < K) ? no_nan(sc[0] + rBlank) : __builtin_huge_valf();
         tb = fmin_sel(tb, xor_lane(tb, 1, lane));
         tb = fmin_sel(tb, xor_lane(tb, 2, lane));
         tb = fmin_sel(tb, xor_lane(tb, 4, lane));
@@ -1503,7 +1500,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
             uint32_t wflat = 0u, wi = 0u, wjj = 0u, wrow = 0u, wbrow = 0u;
 #pragma unroll
             for (int r = 0; r < NC; ++r) {
-              if (cand[r] != kNegInf) {
+              if (cand[r] > kNegInf) {
                 const int i = r / LPT, jj = r % LPT;
                 const int c = tid + jj * kThreads;
                 const uint32_t flat = static_cast<uint32_t>(kslot[i] * W + c);

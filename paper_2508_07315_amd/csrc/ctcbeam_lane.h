@@ -278,13 +278,15 @@ __device__ __forceinline__ float log1p32_unit(float e) {
   const float t = s * q;
   return t + t;
 }
+// a NaN score counts as -inf (the maximum takes the operand that is a number)
+__device__ __forceinline__ float no_nan(float x) { return fmaxf(x, kNegInf); }
 // log(exp(a) + exp(b))
 __device__ __forceinline__ float lse32(float a, float b) {
   const float hi = (a < b) ? b : a;
   const float lo = (a < b) ? a : b;
   if (lo == kNegInf) return hi;
   const float d = lo - hi;
-  if (d < -80.0f) return hi;
+  if (!(d >= -80.0f)) return hi;  // (NaN: both +inf)
   const float e = exp32_nonpos(d);
   const float l = (e < 5.9604645e-8f) ? e : log1p32_unit(e);
   return hi + l;

@@ -336,13 +336,11 @@ __global__ void __launch_bounds__(kST) small_kernel(KernelParams p) {
         const float xe = x + beta;
         x = k_label ? xe : x;
         // the repeat of the beam's last frame label emits nothing; no repeat
-        // after a blank; NaN candidates of labels are none (selects, not
-        // branches)
+        // after a blank; NaN candidates are none (selects, not branches)
         const int off = k_rep ? V : k_emit ? li : -1;
         const int me = k_rep ? li : c;
         x = (me == off) ? kNegInf : x;
-        const float xn = (x == x) ? x : kNegInf;
-        x = k_blank ? x : xn;
+        x = detail::no_nan(x);
         x = k_any ? x : kNegInf;
         const float xo = k_out ? x : kNegInf;  // the best candidate left out of position ei
         if (k_out) x = kNegInf;

@@ -19,3 +19,19 @@ def test_dead_final_scores():
         assert r["nbest_tokens"][0, :, 0].tolist()[0] == 1
         assert r["nbest_lengths"][0, 2] == 0 and r["nbest_tokens"][0, 2, 0] == -1
         assert np.isneginf(r["nbest_scores"][0, 2]) and np.isfinite(r["nbest_scores"][0, :2]).all()
+
+
+def test_nan_scores_are_dead_candidates():
+    """A NaN counts as -inf: the same search as with -inf in its place."""
+    rng = np.random.default_rng(3)
+    V, T = 6, 12
+    lp = np.log(rng.dirichlet(np.ones(V + 1), size=(2, T))).astype(np.float32)
+    nan = rng.random(lp.shape) < 0.3
+    nan[:, 3, V] = True
+    a, b = lp.copy(), lp.copy()
+    a[nan], b[nan] = np.nan, -np.inf
+    lens = np.array([T, T - 2], dtype=np.int32)
+    for kw in ({}, {"logsumexp": True}):
+        x, y = (oracle.decode(q, lens, 8, 0.0, 0.5, want_nbest=True, **kw) for q in (a, b))
+        for k in ("tokens", "lengths", "scores", "nbest_tokens", "nbest_lengths", "nbest_scores"):
+            np.testing.assert_array_equal(x[k], y[k])
