@@ -297,7 +297,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
   const float term_max = fabsf(beta) + (HAS_LM ? fabsf(alpha) * p.lm_absmax : 0.0f) + (HAS_BT ? 64.0f * fabsf(boost_w) : 0.0f);
 
   // upper bound of those terms (a boosted token gains at most one unit)
-  const float term_most = beta + (HAS_LM ? (alpha >= 0.0f ? alpha * p.lm_max : -alpha * p.lm_absmax) : 0.0f) +
+  const float term_most = beta + (HAS_LM ? (alpha >= 0.0f ? alpha * p.lm_max : alpha * p.lm_min) : 0.0f) +
                           (HAS_BT ? (boost_w >= 0.0f ? boost_w : -64.0f * boost_w) : 0.0f);
 
   int rcur = 0;
@@ -966,7 +966,8 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
           float best = kNegInf;
           for (int i = lane; i < gdone * 8; i += 64) best = fmaxf(best, s_top[i]);
           best = wave_max(best, lane);
-          const float R = full ? fminf(best - tb, 32.0f) : 24.0f;
+          // (a best of +inf gives no range)
+          const float R = !(best < __builtin_huge_valf()) ? 0.0f : full ? fminf(best - tb, 32.0f) : 24.0f;
           const float lo = best - R;
           const float scale = 64.0f / R;
           const auto add = [&](float v) __attribute__((always_inline)) {

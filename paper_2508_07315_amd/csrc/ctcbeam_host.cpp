@@ -48,7 +48,7 @@ struct ctcbeam_lm {
   int order = 0, V = 0, nlev = 0;
   int64_t n_states = 0, n_arcs = 0;
   float absmax = 0.0f;           // bound of |ln P| of a finite query
-  float high = 0.0f;             // upper bound of a query
+  float high = 0.0f, low = 0.0f; // upper and lower bound of a query
   std::vector<LmLevel> states;  // [n_states * nlev]
   std::vector<LmArc> arcs;
   std::vector<float> unigram;   // [V+1]
@@ -395,19 +395,24 @@ int build_lm_tables(int order, int V, const int64_t* counts, const int32_t* cons
   lm->n_states = n_states;
   lm->n_arcs = n_arcs;
   // bounds of a query: an entry plus a backoff weight of every level
-  float pmax = 0.0f, bmax = 0.0f, phigh = -std::numeric_limits<float>::infinity(), bhigh = 0.0f;
+  const float inf = std::numeric_limits<float>::infinity();
+  float pmax = 0.0f, bmax = 0.0f, phigh = -inf, bhigh = 0.0f, plow = inf, blow = 0.0f;
   for (int m = 1; m <= order; ++m) {
     for (const float v : ord[m].lnp) {
       if (std::isfinite(v)) pmax = std::max(pmax, std::fabs(v));
       phigh = std::max(phigh, v);
+      plow = std::min(plow, v);
     }
     for (const float v : ord[m].lnbo) {
       if (std::isfinite(v)) bmax = std::max(bmax, std::fabs(v));
       bhigh = std::max(bhigh, v);
+      blow = std::min(blow, v);
     }
   }
   lm->absmax = pmax + static_cast<float>(nlev) * bmax;
-  lm->high = phigh + static_cast<float>(nlev) * bhigh;
+  // (without levels no weight is added: 0 * inf would be NaN)
+  lm->high = phigh + (nlev > 0 ? static_cast<float>(nlev) * bhigh : 0.0f);
+  lm->low = plow + (nlev > 0 ? static_cast<float>(nlev) * blow : 0.0f);
   return 0;
 }
 
@@ -885,6 +890,7 @@ int decode_impl(const float* logprobs, const int32_t* lengths, int B, int T, int
     p.lm_n_states = lm->n_states;
     p.lm_absmax = lm->absmax;
     p.lm_max = lm->high;
+    p.lm_min = lm->low;
     p.lm_bos_state = static_cast<uint32_t>(V);
   }
   if (boost) {

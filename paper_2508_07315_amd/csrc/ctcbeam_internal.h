@@ -100,7 +100,7 @@ struct KernelParams {
   int lm_states_below_2p23;  // every LM state id fits 23 bits
   int64_t lm_n_states;       // number of LM states
   float lm_absmax;           // bound of |ln P| of a finite LM query
-  float lm_max;              // upper bound of an LM query
+  float lm_max, lm_min;      // upper and lower bound of an LM query (entries of -inf count)
   // boosting (null when disabled)
   const BtNode* bt_nodes;
   const BtEntry* bt_list;

@@ -1,6 +1,6 @@
 """GPU parity with NaN log-probabilities in valid frames: a NaN score counts as
--inf for tokens, repeats and blanks alike, in every decoder.  Against the CPU
-oracle, N-best: tokens and lengths equal, scores within 1e-4 (the same fp32
+-inf for tokens, repeats and blanks alike, in every decoder; and with scores of
++inf, which order by index.  Against the CPU oracle, N-best: tokens and lengths equal, scores within 1e-4 (the same fp32
 operations: 0 expected)."""
 import math
 
@@ -92,3 +92,42 @@ def test_nan_scores_greedy(V, order, phrases):
     r = oracle.decode(lp, lens, 1, alpha, 1.0, w, lm=oracle_lm(spec, V) if spec else None,
                       bt=oracle_bt(bspec, V) if bspec else None, n_threads=oracle_threads())
     compare(dict(tokens=tok.cpu().numpy(), lengths=ln.cpu().numpy(), scores=sc.cpu().numpy()), r, what="greedy")
+
+
+@pytest.mark.parametrize("V,K", [(200, 64), (700, 64), (600, 100), (2500, 64)])
+def test_zero_probability_with_negative_alpha(V, K):
+    """A negative LM weight makes +inf of an entry of probability 0.  The only
+    such context is the state of a poor beam, which comes after more than a
+    pass of the class decoder and far below the K-th best of the first pass."""
+    import torch
+    B, T = 3, 3
+    rng = np.random.default_rng([V, K])
+    lp = np.full((B, T, V + 1), -200.0, dtype=np.float32)
+    toks = np.stack([rng.permutation(V)[:80] for _ in range(B)])
+    Z = int(toks[0, 24])
+    for b in range(B):
+        toks[b] = np.where(toks[b] == Z, toks[b, 24], toks[b])
+        toks[b, 24] = Z
+        lp[b, 0, toks[b, :64]] = -np.arange(64)
+        lp[b, 1:][:, toks[b, 64:]] = -0.1 * np.arange(16)
+    lens = np.full(B, T, dtype=np.int32)
+    ids = np.stack([np.full(9, Z, dtype=np.int32), np.sort(rng.permutation(V)[:9]).astype(np.int32)], axis=1)
+    uni = np.full(V + 2, -2.0, dtype=np.float32)
+    # a context of its own for every token
+    pairs = np.array([[c, (c + 1) % V] for c in range(V) if c != Z], dtype=np.int32)
+    bi = np.concatenate([pairs, ids])
+    prob = np.concatenate([np.full(len(pairs), -2.0), np.full(len(ids), -np.inf)]).astype(np.float32)
+    at = np.lexsort((bi[:, 1], bi[:, 0]))
+    arrays = dict(order=2, V=V, ids=[np.arange(V + 2, dtype=np.int32)[:, None], bi[at]], log10_prob=[uni, prob[at]],
+                  log10_bow=[np.zeros(V + 2, dtype=np.float32), None])
+    log("zero probability, negative alpha", V, K)
+    dev = device()
+    tok, ln, sc, ws = P.ctcbeam_decode_nbest(torch.from_numpy(lp).to(dev), torch.from_numpy(lens).to(dev), K, -0.3, 0.0,
+                                             0.0, P.ctcbeam_lm_build(arrays))
+    torch.cuda.synchronize()
+    r = oracle.decode(lp, lens, K, -0.3, 0.0, lm=oracle.LM(arrays), want_nbest=True, n_threads=oracle_threads())
+    assert np.isposinf(r["nbest_scores"]).any()
+    np.testing.assert_array_equal(ln.cpu().numpy(), r["nbest_lengths"])
+    np.testing.assert_array_equal(tok.cpu().numpy(), r["nbest_tokens"])
+    np.testing.assert_allclose(sc.cpu().numpy(), r["nbest_scores"], rtol=0, atol=1e-4)
+    assert P.ctcbeam_query_status(ws) == 0
