@@ -179,8 +179,10 @@ int ctcbeam_decode(const float* logprobs, const int32_t* lengths, int B, int T, 
                                           most 2^23 states, no boosting, and
                                           V of 513..1024 with K <= 8, up to
                                           2048 with K <= 4, up to 4096 with
-                                          K <= 2; the decoder of larger beams
-                                          keeps its rows with either setting) */
+                                          K <= 2, and by the decoder of larger
+                                          beams, which with this flag drops its
+                                          LM and boosting rows at every frame
+                                          and fills them level by level) */
 #define CTCBEAM_FLAG_REPEAT_SCORE 8    /* Sec. III-C's alternative of scoring
                                           repeated emissions at every
                                           occurrence: a frame that repeats the

@@ -431,6 +431,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
         hs[h] = kRows ? ((lms[h] * 0x9E3779B1u) ^ (bts[h] * 0x85EBCA6Bu)) >> 24 : 0u;
         if (alive[h]) atomicMin(&s_cht[hs[h]], static_cast<uint32_t>(lane + 64 * h));
       }
+      wave_lds_fence();
 #pragma unroll
       for (int h = 0; h < SPL; ++h) ld[h] = alive[h] ? static_cast<int>(s_cht[hs[h]]) : lane + 64 * h;
       float lx[SPL];
@@ -453,6 +454,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
         }
         CT += __popcll(m);
       }
+      wave_lds_fence();
 #pragma unroll
       for (int h = 0; h < SPL; ++h) {
         cls[h] = alive[h] ? static_cast<int>(s_cid[ld[h]]) : -1;
@@ -467,6 +469,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
         for (int h = 0; h < SPL; ++h)
           if (alive[h] && sc[h] > lx[h])
             atomicMax(&s_ctop[cls[h]], static_cast<unsigned long long>(order_key(sc[h], static_cast<uint32_t>(lane + 64 * h))));
+        wave_lds_fence();
 #pragma unroll
         for (int h = 0; h < SPL; ++h) {
           const uint64_t top = alive[h] ? s_ctop[cls[h]] : 0ull;  // 0: the leading slot
@@ -475,6 +478,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
           if (top != 0ull ? ~static_cast<uint32_t>(top) == static_cast<uint32_t>(lane + 64 * h) : lead[h])
             s_cj[cls[h]] = static_cast<uint8_t>(lane + 64 * h);
         }
+        wave_lds_fence();
       }
     }
     // the rows of live states
@@ -606,6 +610,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
               s_xpid[kind][n & 15] = pd;
             }
             live |= static_cast<uint32_t>(__ballot(taken));
+            wave_lds_fence();
             const uint32_t nk = s_xkey[kind][at & 15];
             tag = taken ? nk : tag;
             const uint32_t nfi = lane_get(static_cast<uint32_t>(n), fi);
@@ -620,9 +625,10 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
             for (int i = 0; i < 16; ++i) {
               if (i >= M) break;  // uniform
               if (lane == i) tbl[row_hash(fr_key)] = static_cast<uint8_t>(fr_row);
-              __builtin_amdgcn_wave_barrier();
+              wave_lds_fence();
             }
-            hand = static_cast<int>(rdlane(fr_row, M - 1) + 1u) & 31;
+            // (no row is free where the first class has one and fills the area)
+            if (M > 0) hand = static_cast<int>(rdlane(fr_row, M - 1) + 1u) & 31;
             nf = M;
           }
           return static_cast<uint32_t>(q);
@@ -1074,6 +1080,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
               if (lane == 0) s_over = 1;
               nh = kHot;
             }
+            wave_lds_fence();
             CTCBEAM_PHASE_ADD(19, nh);  // pairs expanded
             for (int h0 = 0; h0 < nh; h0 += 64) {
               // lane i: pair h0 + i
