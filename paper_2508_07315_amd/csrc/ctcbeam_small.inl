@@ -340,8 +340,8 @@ __global__ void __launch_bounds__(kST) small_kernel(KernelParams p) {
         const int off = k_rep ? V : k_emit ? li : -1;
         const int me = k_rep ? li : c;
         x = (me == off) ? kNegInf : x;
-        x = detail::no_nan(x);
-        x = k_any ? x : kNegInf;
+        const float xn = (x == x) ? x : kNegInf;
+        x = k_any ? xn : kNegInf;
         const float xo = k_out ? x : kNegInf;  // the best candidate left out of position ei
         if (k_out) x = kNegInf;
         const bool evalid = x != kNegInf;
