@@ -125,6 +125,7 @@ constexpr uint32_t kStateMask = (1u << kOrderShift) - 1u;
 constexpr int kLdsBytes = 160 * 1024;
 constexpr int kCT = kClassThreads;
 constexpr int kCW = kCT / 64;  // waves of a workgroup
+static_assert(kCW == 8, "8 label groups a class, one a wave");
 
 // LPT = labels per lane.  NLEV = levels of the LM's backoff chain above the
 // unigrams (-1: no LM).  SPL = beam slots per lane: slot j lives in lane
@@ -213,8 +214,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
   // Labels run over the workgroup; vocabularies of at most half of it are
   // held by nb waves, and the kCW / nb sets of waves share the classes, so
   // that a character vocabulary does not leave waves idle.
-  constexpr int kLgW = kCW == 8 ? 3 : 2;
-  const int lgnb = LPT > 1 ? kLgW : V <= 64 ? 0 : V <= 128 ? 1 : V <= 256 ? 2 : kLgW;
+  const int lgnb = LPT > 1 ? 3 : V <= 64 ? 0 : V <= 128 ? 1 : V <= 256 ? 2 : 3;
   const int nb = 1 << lgnb, nsub = kCW >> lgnb;
   const int sub = LPT > 1 ? 0 : wave >> lgnb;
   const int wblk = wave & (nb - 1);
@@ -512,7 +512,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
         float dm = s_dm[lane & (kCW - 1)];
         dm = fmaxf(dm, xor_lane(dm, 1, lane));
         dm = fmaxf(dm, xor_lane(dm, 2, lane));
-        if (kCW == 8) dm = fmaxf(dm, xor_lane(dm, 4, lane));
+        dm = fmaxf(dm, xor_lane(dm, 4, lane));
         int keep = 0;
 #pragma unroll
         for (int h = 0; h < SPL; ++h) {
@@ -908,7 +908,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
             float m1 = fmaxf(b2 ? m2[1] : m2[0], xor_lane(b2 ? m2[0] : m2[1], 4, lane));
             if (lgnb >= 1) m1 = fmaxf(m1, xor_lane(m1, 8, lane));
             if (lgnb >= 2) m1 = fmaxf(m1, xor_lane(m1, 16, lane));
-            if (kLgW >= 3 && lgnb >= 3) m1 = fmaxf(m1, xor_lane(m1, 32, lane));
+            if (lgnb >= 3) m1 = fmaxf(m1, xor_lane(m1, 32, lane));
             const int r = s8 + ((lane & 1) << 2) + (lane & 2) + ((lane >> 2) & 1);
             const int q = sub + r * nsub;
             if ((lane & ((8 << lgnb) - 1)) < 8 && q < nq)
@@ -986,12 +986,8 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
             const bool in = cls[h] >= 0 && cls[h] < gdone;
             const int lg0 = last[h] == V ? -1 : group_of(last[h]);
             const float d = smx[h] - sc[h];
-#pragma unroll
-            for (int i = 0; i < 8 / kCW; ++i) {
-              const int g = wave * (8 / kCW) + i;
-              const float m = s_top[(in ? cls[h] : 0) * 8 + g];
-              if (in && g != lg0) add(lower(m, d));
-            }
+            const float m = s_top[(in ? cls[h] : 0) * 8 + wave];
+            if (in && wave != lg0) add(lower(m, d));
             if (wave == 0 && alive[h]) add(xblank[h]);
             if (wave == 1) add(xrep[h]);
           }
@@ -1367,7 +1363,7 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
           if (SPL > 1 && h > 0) low |= __ballot(klo[0] == l0 && khi[0] == h0);
           if (low != 0ull) mine[h] |= (1ull << i) & live;
         }
-        if (lane < 8 / kCW) s_dup[wave * (8 / kCW) + lane][h] = mine[h];
+        if (lane == 0) s_dup[wave][h] = mine[h];
       }
       __syncthreads();
 #pragma unroll

@@ -53,10 +53,11 @@
 //      fetched while the ranking runs).
 //   U. update: prune, recombine, take the new beam into registers, plan the
 //      next frame's chunks, write back-pointers to HBM.
-// Large beams (K*V above the key rows) repeat F/C/T per chunk of beams with
-// a running bound and rank the pool only when it fills up or after the last
-// chunk.  A survivor pool overflow falls back to an exact extraction.  After the last frame the best beam is traced back through the
-// back-pointers staged in LDS.
+// Beams over one chunk (K*V above the key rows) repeat F/C/T per chunk of
+// beams with a running bound and rank the pool only when it fills up or after
+// the last chunk.  A survivor pool overflow falls back to an exact extraction.
+// After the last frame the best beam is traced back through the back-pointers
+// staged in LDS.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -79,8 +80,8 @@ constexpr uint32_t kTargetMask = (1u << 23) - 1u;
 // ctcbeam_internal.h): each wave adds the s_memtime cycles of every phase of
 // every frame (fill, barrier A, candidates, barrier B, filter, barrier C,
 // rank, barrier D, the update's remainder; then the frame and chunk counts;
-// then, one slot per lane, the update's prune + recombination, new state and
-// chunk plan; then the bound, split from the filter) and writes them after the [B, 8] statistics as
+// then the update's prune + recombination, new state and chunk plan; then the
+// bound, split from the filter) and writes them after the [B, 8] statistics as
 // [B, kWaves, kPhaseWords] int64.
 
 // SKIP: ranks of chunks before the last are skipped while the survivor pool
@@ -95,12 +96,11 @@ constexpr uint32_t kTargetMask = (1u << 23) - 1u;
 // rest.
 template <int LPT, int NLEV, bool HAS_BT, bool SKIP, bool CACHE, bool REP>
 __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
-  constexpr int SPL = 1;                      // beam slots per lane
   constexpr bool HAS_LM = NLEV >= 0;
   constexpr int NL = NLEV > 0 ? NLEV : 0;     // chain levels above the unigram root
   constexpr int NLA = NL > 0 ? NL : 1;        // array extent
   constexpr int NF = NL > 1 ? NL - 1 : 1;     // backoff weights folded into an arc (extent)
-  constexpr int KMX = 64 * SPL;               // slot capacity
+  constexpr int KMX = 16;                     // slot capacity
   constexpr int KCR = 16 / LPT;               // beams (key rows) per chunk
   // LDS scratch carved from one block so the traceback can reuse it:
   // [LM rows: KW x u64][boosting rows: KW x u32][LM targets: kLmStage]
@@ -123,19 +123,17 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   constexpr int kBtTU = 1;
   static_assert(!CACHE || (kSmallK && HAS_LM && NL > 0 && !HAS_BT), "row caching needs one chunk and an LM");
   // The key rows hold the unigram + backoff fold of every token (as order-0
-  // entries) with row caching, and for chains of four or more levels with
-  // one slot per lane, whose backoff weights would otherwise take KCR x NL
-  // registers in the scoring.  Shorter chains, and the many chunks of two
-  // slots per lane, fold in the scoring: cheaper than the extra LDS maxima.
+  // entries) with row caching, and for chains of four or more levels, whose
+  // backoff weights would otherwise take KCR x NL registers in the scoring.
+  // Shorter chains fold in the scoring: cheaper than the extra LDS maxima.
   constexpr bool kFoldRows = CACHE || NL >= 4;
   // Fill groups (beams over one chunk, no row cache): the update orders the
   // live beams by LM state and cuts that order into groups of consecutive
   // chunks whose distinct LM states (at most KSEG), boosting lists (at most
   // KCR - 1) and staged arcs (at most kLmStage) fit the rows (a state whose
-  // own lists exceed a group is split by list).  A state or list has one row per group,
-  // filled at the group's first chunk; the group's other chunks skip the
-  // fill and its barrier.  Large beams hold few distinct states and lists
-  // (at K = 64 about 10 and 6), so a frame fills about two groups.
+  // own lists exceed a group is split by list).  A state or list has one row
+  // per group, filled at the group's first chunk; the group's other chunks
+  // skip the fill and its barrier.
   constexpr bool kGroups = !CACHE && SKIP && (HAS_LM || HAS_BT);
   constexpr int kRowWords = kFoldRows ? 4 : 16;  // beam record per live position
   // beam state record (one per slot, double-buffered by frame): score bits,
@@ -170,7 +168,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   // beam state records by slot: [rcur] the current beam, [rcur ^ 1] its successors
   __shared__ __align__(16) uint32_t s_rec[2 * KMX * RW];
   // group maxima of the bound; K <= 8: (row, wave) maxima, then wave maxima
-  __shared__ float s_top[kWaves * 8 * SPL + kWaves];
+  __shared__ float s_top[kWaves * 8 + kWaves];
   __shared__ uint64_t s_red[2][kWaves];
   __shared__ int32_t s_nbuf, s_overflow;
   __shared__ int32_t s_best, s_bestlen;
@@ -226,46 +224,27 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   float rBlankN = (L > 0 && lane < K) ? Db[V] : 0.0f;
   float rBlank = 0.0f;
 
-  // ---- beam state: slot j = lane + 64 h in register set h, replicated in
-  // every wave ----
+  // ---- beam state: slot j = lane, replicated in every wave ----
   const int j = lane;
-  float sc[SPL];
-  int32_t last[SPL], len[SPL];
-  uint32_t lvb[SPL][NLA], lvc[SPL][NLA];
-  float lvbo[SPL][NLA];
-  uint32_t btb[SPL], btc[SPL];
-  int32_t btpot[SPL];
-  bool alive[SPL];
-  // kGroups: fill group of slot j + 64 h (-1: dead), its LM and boosting
-  // rows there and whether the slot fills them; lane q of gch0[h]: the first
-  // chunk of group q + 64 h (at most one group per live slot)
-  int grp[SPL], lrow_g[SPL], brow_g[SPL], gch0[SPL];
-  bool lown[SPL], bown[SPL];
+  float sc = (j == 0) ? 0.0f : kNegInf;
+  int32_t last = V, len = 0;
+  uint32_t lvb[NLA], lvc[NLA];
+  float lvbo[NLA];
 #pragma unroll
-  for (int h = 0; h < SPL; ++h) {
-    grp[h] = 0;
-    lrow_g[h] = 0;
-    brow_g[h] = 0;
-    gch0[h] = 0;
-    lown[h] = bown[h] = h == 0 && j == 0;
+  for (int l = 0; l < NLA; ++l) {
+    lvb[l] = 0u;
+    lvc[l] = 0u;
+    lvbo[l] = 0.0f;
   }
+  uint32_t btb = 0u, btc = 0u;
+  int32_t btpot = 0;
+  bool alive = j == 0;
+  // kGroups: fill group of slot j (-1: dead), its LM and boosting rows there
+  // and whether the slot fills them; lane q of gch0: the first chunk of group
+  // q (at most one group per live slot)
+  int grp = 0, lrow_g = 0, brow_g = 0, gch0 = 0;
+  bool lown = j == 0, bown = j == 0;
   int ngrp = 1;
-#pragma unroll
-  for (int h = 0; h < SPL; ++h) {
-    sc[h] = (h == 0 && j == 0) ? 0.0f : kNegInf;
-    last[h] = V;
-    len[h] = 0;
-#pragma unroll
-    for (int l = 0; l < NLA; ++l) {
-      lvb[h][l] = 0u;
-      lvc[h][l] = 0u;
-      lvbo[h][l] = 0.0f;
-    }
-    btb[h] = 0u;
-    btc[h] = 0u;
-    btpot[h] = 0;
-    alive[h] = h == 0 && j == 0;
-  }
 #ifdef CTCBEAM_PHASE_CLOCKS
   // profiling builds: the stats buffer takes the phase clocks, and the
   // counters stay off so that the phases time what a plain launch runs
@@ -278,16 +257,16 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
 #pragma unroll
       for (int l = 0; l < NL; ++l) {
         const LmLevel hd = p.lm_states[static_cast<size_t>(p.lm_bos_state) * NL + l];
-        lvb[0][l] = hd.begin;
-        lvc[0][l] = hd.count;
-        lvbo[0][l] = hd.bo;
+        lvb[l] = hd.begin;
+        lvc[l] = hd.count;
+        lvbo[l] = hd.bo;
       }
     }
     if (HAS_BT) {
       const BtNode nd = p.bt_nodes[0];
-      btb[0] = nd.list_begin;
-      btc[0] = nd.list_count;
-      btpot[0] = static_cast<int32_t>(nd.pot & 0xFFu);
+      btb = nd.list_begin;
+      btc = nd.list_count;
+      btpot = static_cast<int32_t>(nd.pot & 0xFFu);
     }
   }
   // Row cache (CACHE): lane r < KCR holds the LM state of key row r; lane j
@@ -300,25 +279,22 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
     rtag = p.lm_bos_state;
     fillrep = true;
   }
-  // beam record of live position lp for slot j + 64 h (written by wave 0 for
-  // the live slots); with CACHE the slot field also carries the key row
-  // (bits 8..15)
-  auto put_row = [&](int lp, int h) __attribute__((always_inline)) {
+  // beam record of live position lp for slot j (the live slots write it); with
+  // CACHE the slot field also carries the key row (bits 8..15)
+  auto put_row = [&](int lp) __attribute__((always_inline)) {
     uint32_t* rr = s_row + lp * kRowWords;
-    const uint32_t zf = static_cast<uint32_t>(j + 64 * h) | (CACHE ? static_cast<uint32_t>(rowof) << 8 : 0u) |
-                        (kGroups ? (static_cast<uint32_t>(lrow_g[h]) << 8) | (static_cast<uint32_t>(brow_g[h]) << 16) : 0u);
-    *reinterpret_cast<uint4*>(rr) = make_uint4(__float_as_uint(sc[h]), static_cast<uint32_t>(last[h]),
-                                               zf, static_cast<uint32_t>(btpot[h]));
+    const uint32_t zf = static_cast<uint32_t>(j) | (CACHE ? static_cast<uint32_t>(rowof) << 8 : 0u) |
+                        (kGroups ? (static_cast<uint32_t>(lrow_g) << 8) | (static_cast<uint32_t>(brow_g) << 16) : 0u);
+    *reinterpret_cast<uint4*>(rr) = make_uint4(__float_as_uint(sc), static_cast<uint32_t>(last),
+                                               zf, static_cast<uint32_t>(btpot));
 #pragma unroll
     for (int l0 = 0; l0 < (kFoldRows ? 0 : NL); l0 += 4) {
-      const auto bo_at = [&](int l) __attribute__((always_inline)) { return l < NL ? __float_as_uint(lvbo[h][l < NLA ? l : 0]) : 0u; };
+      const auto bo_at = [&](int l) __attribute__((always_inline)) { return l < NL ? __float_as_uint(lvbo[l < NLA ? l : 0]) : 0u; };
       *reinterpret_cast<uint4*>(rr + 4 + l0) = make_uint4(bo_at(l0), bo_at(l0 + 1), bo_at(l0 + 2), bo_at(l0 + 3));
     }
   };
   // chunk plan: chunk id of each live slot, number of chunks (uniform)
-  int cid[SPL];
-#pragma unroll
-  for (int h = 0; h < SPL; ++h) cid[h] = 0;
+  int cid = 0;
   int nch = 1;
   // kGroups: the fill-group plan of the next frame from the new beam (nal:
   // live slots, ac: staged arcs, lk: LM state keys).  LM states are taken in
@@ -331,211 +307,103 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   // most KCR - 1 lists: beams without a list read row KCR - 1, which the
   // group's fill leaves empty.  Sets the live positions lpos, the group
   // fields and chunk ids of the slots, nch, ngrp and gch0.
-  const auto plan_groups = [&](const bool (&nal)[SPL], const int32_t (&ac)[SPL], const uint32_t (&lk)[SPL],
-                               int (&lpos)[SPL]) __attribute__((always_inline)) {
-    const auto any = [&](const uint64_t (&m)[SPL]) __attribute__((always_inline)) {
-      bool r = false;
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) r = r || m[h] != 0ull;
-      return r;
-    };
-    // the register set holding the lowest slot of a non-empty mask
-    const auto low_set = [&](const uint64_t (&m)[SPL]) __attribute__((always_inline)) {
-      int hs = SPL - 1;
-#pragma unroll
-      for (int h = SPL - 1; h >= 0; --h) hs = m[h] != 0ull ? h : hs;
-      return hs;
-    };
+  const auto plan_groups = [&](bool nal, int32_t ac, uint32_t lk, int& lpos) __attribute__((always_inline)) {
     const auto rd64 = [&](uint64_t v, int l) __attribute__((always_inline)) {
       return (static_cast<uint64_t>(rdlane(static_cast<uint32_t>(v >> 32), l)) << 32) |
              rdlane(static_cast<uint32_t>(v), l);
     };
-    uint64_t rem[SPL], hbm[SPL];
-    bool hasb[SPL], lead[SPL];
-    int bl[SPL];             // leader of the slot's boosting list
-    uint64_t lmk[SPL][SPL];  // the slots holding the slot's list, by register set
-#pragma unroll
-    for (int h = 0; h < SPL; ++h) {
-      rem[h] = __ballot(nal[h]);
-      hasb[h] = HAS_BT && nal[h] && btc[h] != 0u;
-      hbm[h] = __ballot(hasb[h]);
-      lead[h] = false;
-      bl[h] = 0;
-#pragma unroll
-      for (int hh = 0; hh < SPL; ++hh) lmk[h][hh] = 0ull;
-      grp[h] = -1;
-      lrow_g[h] = 0;
-      brow_g[h] = KCR - 1;
-      lown[h] = bown[h] = false;
-      cid[h] = -1;
-      gch0[h] = 0x7FFFFFFF;
-    }
+    uint64_t rem = __ballot(nal);
+    const bool hasb = HAS_BT && nal && btc != 0u;
+    const uint64_t hbm = __ballot(hasb);
+    bool lead = false;
+    int bl = 0;           // leader of the slot's boosting list
+    uint64_t lmk = 0ull;  // the slots holding the slot's list
+    grp = -1;
+    lrow_g = 0;
+    brow_g = KCR - 1;
+    lown = bown = false;
+    cid = -1;
+    gch0 = 0x7FFFFFFF;
     if constexpr (HAS_BT) {
       // the distinct lists (begin, count): one a pass
-      uint64_t brem[SPL];
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) brem[h] = hbm[h];
-      while (any(brem)) {  // uniform
-        const int hl = low_set(brem);
-        int jl = 0;
-        uint32_t b0 = 0u, c0 = 0u;
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) {
-          if (h == hl) {
-            jl = static_cast<int>(__builtin_ctzll(brem[h]));
-            b0 = rdlane(btb[h], jl);
-            c0 = rdlane(btc[h], jl);
-          }
-        }
-        uint64_t m[SPL];
-#pragma unroll
-        for (int hh = 0; hh < SPL; ++hh) {
-          m[hh] = __ballot(hasb[hh] && btb[hh] == b0 && btc[hh] == c0);
-          brem[hh] &= ~m[hh];
-        }
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) {
-          if ((m[h] >> j) & 1ull) {
-            bl[h] = jl + 64 * hl;
-#pragma unroll
-            for (int hh = 0; hh < SPL; ++hh) lmk[h][hh] = m[hh];
-          }
+      uint64_t brem = hbm;
+      while (brem != 0ull) {  // uniform
+        const int jl = static_cast<int>(__builtin_ctzll(brem));
+        const uint32_t b0 = rdlane(btb, jl), c0 = rdlane(btc, jl);
+        const uint64_t m = __ballot(hasb && btb == b0 && btc == c0);
+        brem &= ~m;
+        if ((m >> j) & 1ull) {
+          bl = jl;
+          lmk = m;
         }
       }
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) lead[h] = hasb[h] && bl[h] == j + 64 * h;
+      lead = hasb && bl == j;
     }
     int pos = 0, g = -1, chn = 0;
     int g_rows = 0, g_arcs = 0, g_beams = 0;
-    uint64_t g_bl[SPL], g_mem[SPL];  // the open group's lists (by leader) and members
-#pragma unroll
-    for (int h = 0; h < SPL; ++h) g_bl[h] = g_mem[h] = 0ull;
+    uint64_t g_bl = 0ull, g_mem = 0ull;  // the open group's lists (by leader) and members
     // the open group's chunks, and its members' boosting rows and fillers
     const auto close_group = [&]() __attribute__((always_inline)) {
       if (g < 0) return;
       chn += (g_beams + KCR - 1) / KCR;
       if constexpr (HAS_BT) {
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) {
-          if (grp[h] == g && hasb[h]) {
-            const int L = bl[h];
-            int r = 0;
-            bool first = true;
-#pragma unroll
-            for (int hh = 0; hh < SPL; ++hh) {
-              const uint64_t lead_below =
-                  hh < (L >> 6) ? ~0ull : (hh == (L >> 6) ? ((1ull << (L & 63)) - 1ull) : 0ull);
-              r += __popcll(g_bl[hh] & lead_below);
-              const uint64_t slot_below = hh < h ? ~0ull : (hh == h ? lmlt : 0ull);
-              first = first && (lmk[h][hh] & g_mem[hh] & slot_below) == 0ull;
-            }
-            brow_g[h] = r;
-            bown[h] = first;
-          }
+        if (grp == g && hasb) {
+          brow_g = __popcll(g_bl & ((1ull << bl) - 1ull));
+          bown = (lmk & g_mem & lmlt) == 0ull;
         }
       }
     };
     const auto open_group = [&](int a) __attribute__((always_inline)) {
       close_group();
       ++g;
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        if (h == (g >> 6) && lane == (g & 63)) gch0[h] = chn;
-        g_bl[h] = g_mem[h] = 0ull;
-      }
+      if (lane == g) gch0 = chn;
+      g_bl = g_mem = 0ull;
       g_rows = 0;
       g_arcs = 0;
       g_beams = 0;
       if (a > kLmStage) status |= 4u;  // a single chain above the staging limit (the builders prevent it)
     };
-    // the beams sub join the open group with LM row srow (filled by beam
-    // (hs, js) when the row is new) and bring the lists nl
-    const auto place = [&](const uint64_t (&sub)[SPL], const uint64_t (&nl)[SPL], int srow, bool newrow, int hs,
-                           int js) __attribute__((always_inline)) {
-      int before = 0;  // members in the lower register sets
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        if ((sub[h] >> j) & 1ull) {
-          const int inq = before + __popcll(sub[h] & lmlt);
-          lpos[h] = pos + inq;
-          cid[h] = chn + (g_beams + inq) / KCR;
-          grp[h] = g;
-          lrow_g[h] = srow;
-          lown[h] = newrow && h == hs && j == js;
-        }
-        before += __popcll(sub[h]);
-        g_mem[h] |= sub[h];
-        g_bl[h] |= nl[h];
+    // the beams sub join the open group with LM row srow (filled by beam js
+    // when the row is new) and bring the lists nl
+    const auto place = [&](uint64_t sub, uint64_t nl, int srow, bool newrow, int js) __attribute__((always_inline)) {
+      if ((sub >> j) & 1ull) {
+        const int inq = __popcll(sub & lmlt);
+        lpos = pos + inq;
+        cid = chn + (g_beams + inq) / KCR;
+        grp = g;
+        lrow_g = srow;
+        lown = newrow && j == js;
       }
-      g_beams += before;
-      pos += before;
+      g_mem |= sub;
+      g_bl |= nl;
+      g_beams += __popcll(sub);
+      pos += __popcll(sub);
     };
-    while (any(rem)) {  // uniform: one LM state a pass
-      const int hs = low_set(rem);
-      int js = 0, a = 0;
-      uint32_t sk = 0u;
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        if (h == hs) {
-          js = static_cast<int>(__builtin_ctzll(rem[h]));
-          sk = rdlane(lk[h], js);
-          a = rdlane(ac[h], js);
-        }
-      }
-      uint64_t smem[SPL], sl[SPL];
-      int nsl = 0, nu = 0;
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        smem[h] = __ballot(nal[h] && lk[h] == sk);
-        rem[h] &= ~smem[h];
-      }
+    while (rem != 0ull) {  // uniform: one LM state a pass
+      const int js = static_cast<int>(__builtin_ctzll(rem));
+      const uint32_t sk = rdlane(lk, js);
+      const int a = rdlane(ac, js);
+      uint64_t smem = __ballot(nal && lk == sk);
+      rem &= ~smem;
       // the state's lists, by leader
-#pragma unroll
-      for (int h = 0; h < SPL; ++h) {
-        bool pres = false;
-#pragma unroll
-        for (int hh = 0; hh < SPL; ++hh) pres = pres || (lmk[h][hh] & smem[hh]) != 0ull;
-        sl[h] = __ballot(lead[h] && pres);
-        nsl += __popcll(sl[h]);
-        nu += __popcll(sl[h] | g_bl[h]);
-      }
-      if (nsl <= KCR - 1) {  // uniform: the whole state joins one group
-        if (!(g >= 0 && g_rows < KSEG && g_arcs + a <= kLmStage && nu <= KCR - 1)) open_group(a);
+      const uint64_t sl = __ballot(lead && (lmk & smem) != 0ull);
+      if (__popcll(sl) <= KCR - 1) {  // uniform: the whole state joins one group
+        if (!(g >= 0 && g_rows < KSEG && g_arcs + a <= kLmStage && __popcll(sl | g_bl) <= KCR - 1)) open_group(a);
         const int srow = g_rows++;
         g_arcs += a;
-        place(smem, sl, srow, true, hs, js);
+        place(smem, sl, srow, true, js);
       } else {
         // the state's lists exceed a group: one list a pass (beams without a
         // list with the lowest slot's pass)
         int srow = -1;
-        while (any(smem)) {  // uniform
-          const int hb = low_set(smem);
-          int jb = 0, L = 0;
-          bool lb = false;
-#pragma unroll
-          for (int h = 0; h < SPL; ++h) {
-            if (h == hb) {
-              jb = static_cast<int>(__builtin_ctzll(smem[h]));
-              lb = ((hbm[h] >> jb) & 1ull) != 0ull;
-              L = rdlane(bl[h], jb);
-            }
-          }
-          uint64_t sub[SPL], nl[SPL];
-          bool newl = false;
-          int nb = 0;
-#pragma unroll
-          for (int hh = 0; hh < SPL; ++hh) {
-            uint64_t mk = 0ull;
-#pragma unroll
-            for (int h = 0; h < SPL; ++h)
-              if (h == hb) mk = rd64(lmk[h][hh], jb);
-            sub[hh] = smem[hh] & (lb ? mk : ~hbm[hh]);
-            nl[hh] = (lb && hh == (L >> 6)) ? (1ull << (L & 63)) : 0ull;
-            newl = newl || (nl[hh] & ~g_bl[hh]) != 0ull;
-            nb += __popcll(g_bl[hh]);
-          }
+        while (smem != 0ull) {  // uniform
+          const int jb = static_cast<int>(__builtin_ctzll(smem));
+          const bool lb = ((hbm >> jb) & 1ull) != 0ull;
+          const uint64_t sub = smem & (lb ? rd64(lmk, jb) : ~hbm);
+          const uint64_t nl = lb ? 1ull << rdlane(bl, jb) : 0ull;
+          const bool newl = (nl & ~g_bl) != 0ull;
           const bool fits = g >= 0 && (srow >= 0 || (g_rows < KSEG && g_arcs + a <= kLmStage)) &&
-                            (!newl || nb < KCR - 1);
+                            (!newl || __popcll(g_bl) < KCR - 1);
           if (!fits) {
             open_group(a);
             srow = -1;
@@ -545,9 +413,8 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
             srow = g_rows++;
             g_arcs += a;
           }
-          place(sub, nl, srow, newrow, hb, jb);
-#pragma unroll
-          for (int hh = 0; hh < SPL; ++hh) smem[hh] &= ~sub[hh];
+          place(sub, nl, srow, newrow, jb);
+          smem &= ~sub;
         }
       }
     }
@@ -638,7 +505,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
     for (int i = tid; i < 2 * KMX; i += kThreads) s_rinc[i / KMX][i % KMX] = make_float2(0.0f, 0.0f);
   __syncthreads();
   if (tid == 0) {
-    put_row(0, 0);
+    put_row(0);
     // record of the initial beam (slot 0)
     uint32_t r[RW];
 #pragma unroll
@@ -646,15 +513,15 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
     r[kRLast] = static_cast<uint32_t>(V);
     r[kRLms] = HAS_LM ? p.lm_bos_state : 0u;
     if (HAS_BT) {
-      r[kRBtb] = btb[0];
-      r[kRBtc] = btc[0];
-      r[kRBtp] = static_cast<uint32_t>(btpot[0]);
+      r[kRBtb] = btb;
+      r[kRBtc] = btc;
+      r[kRBtp] = static_cast<uint32_t>(btpot);
     }
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-      r[kRLvb + l] = lvb[0][l];
-      r[kRLvc + l] = lvc[0][l];
-      r[kRLvbo + l] = __float_as_uint(lvbo[0][l]);
+      r[kRLvb + l] = lvb[l];
+      r[kRLvc + l] = lvc[l];
+      r[kRLvbo + l] = __float_as_uint(lvbo[l]);
     }
     store_rec(s_rec, r);
     s_nbuf = 0;
@@ -664,9 +531,9 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       unsigned long long ns = 0, na = 0;
 #pragma unroll
       for (int l = 0; l < NL; ++l) {
-        if (L > 0 && (lvc[0][l] & kExists)) {
+        if (L > 0 && (lvc[l] & kExists)) {
           ns += 1;
-          na += lvc[0][l] & ~kExists;
+          na += lvc[l] & ~kExists;
         }
       }
       s_st[0] = L > 0 ? 1 : 0;
@@ -709,22 +576,15 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
 
     for (int ch = 0; ch < nch; ++ch) {
       // this chunk's beams and their key rows (slot order)
-      bool inch[SPL];
-      int row[SPL];
-      int kc = 0;
-      inch[0] = alive[0] && (cid[0] == ch);
-      const uint64_t chmask = __ballot(inch[0]);
-      kc = __popcll(chmask);
-      row[0] = __popcll(chmask & lmlt);
+      const bool inch = alive && (cid == ch);
+      const uint64_t chmask = __ballot(inch);
+      const int kc = __popcll(chmask);
+      const int row = __popcll(chmask & lmlt);
 
       // ---- F. fill the key rows of this chunk (of its group) ----
       // kGroups: only a group's first chunk fills (uniform)
       bool gfill = !kGroups;
-      if constexpr (kGroups) {
-#pragma unroll
-        for (int h = 0; h < SPL; ++h)
-          if (h == (gi >> 6)) gfill = gi < ngrp && ch == rdlane(gch0[h], gi & 63);
-      }
+      if constexpr (kGroups) gfill = gi < ngrp && ch == rdlane(gch0, gi & 63);
       if (gfill) {  // uniform
         if (gen == kGenMax) {
           // rows were last read before the previous filter barrier
@@ -749,65 +609,59 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
         for (int k = 0; k < NF; ++k) sg_f[k] = 0.0f;
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
+          // the beams that fill an LM row (the row's first with fill groups)
+          const bool fsel = CACHE ? fillrep : kGroups ? (alive && grp == gi && lown) : inch;
+          const uint32_t n = fsel ? (lvc[l] & ~kExists) : 0u;
+          const uint64_t m = __ballot(n != 0u);
+          const int nl = __popcll(m);
+          if (nl > 0) {  // wave-uniform
+            // senders push to their segment lane; the rest to a lane outside
+            // [S, S + nl) (S + nl <= 64)
+            const int dst = (n != 0u) ? S + __popcll(m & lmlt) : ((S + nl) & 63);
+            const int addr = dst << 2;
+            const uint32_t r_cnt = static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, static_cast<int>(n)));
+            const uint32_t r_base =
+                static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, static_cast<int>(lvb[l])));
+            const uint32_t r_rl =
+                static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, (CACHE ? rowof : kGroups ? lrow_g : row) | (l << 8)));
+            float r_f[NF];
 #pragma unroll
-          for (int h = 0; h < SPL; ++h) {
-            // the beams that fill an LM row (the row's first with fill groups)
-            const bool fsel = CACHE ? fillrep : kGroups ? (alive[h] && grp[h] == gi && lown[h]) : inch[h];
-            const uint32_t n = fsel ? (lvc[h][l] & ~kExists) : 0u;
-            const uint64_t m = __ballot(n != 0u);
-            const int nl = __popcll(m);
-            if (nl > 0) {  // wave-uniform
-              // senders push to their segment lane; the rest to a lane outside
-              // [S, S + nl) (S + nl <= 64)
-              const int dst = (n != 0u) ? S + __popcll(m & lmlt) : ((S + nl) & 63);
-              const int addr = dst << 2;
-              const uint32_t r_cnt = static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, static_cast<int>(n)));
-              const uint32_t r_base =
-                  static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, static_cast<int>(lvb[h][l])));
-              const uint32_t r_rl =
-                  static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, (CACHE ? rowof : kGroups ? lrow_g[h] : row[h]) | (l << 8)));
-              float r_f[NF];
-#pragma unroll
-              for (int k = 0; k + 1 < NL; ++k) {
-                const int lk = l + 1 + k;
-                const float fk = lk < NL ? lvbo[h][lk < NLA ? lk : 0] : 0.0f;
-                r_f[k] = __int_as_float(__builtin_amdgcn_ds_permute(addr, __float_as_int(fk)));
-              }
-              if (lane >= S && lane < S + nl) {
-                sg_cnt = r_cnt;
-                sg_base = r_base;
-                sg_rl = r_rl;
-#pragma unroll
-                for (int k = 0; k + 1 < NL; ++k) sg_f[k] = r_f[k];
-              }
-              S += nl;
+            for (int k = 0; k + 1 < NL; ++k) {
+              const int lk = l + 1 + k;
+              const float fk = lk < NL ? lvbo[lk < NLA ? lk : 0] : 0.0f;
+              r_f[k] = __int_as_float(__builtin_amdgcn_ds_permute(addr, __float_as_int(fk)));
             }
+            if (lane >= S && lane < S + nl) {
+              sg_cnt = r_cnt;
+              sg_base = r_base;
+              sg_rl = r_rl;
+#pragma unroll
+              for (int k = 0; k + 1 < NL; ++k) sg_f[k] = r_f[k];
+            }
+            S += nl;
           }
         }
         if constexpr (!CACHE && kFoldRows) {
           // every token of every row of the chunk gets its unigram + backoff
           // fold as an order-0 entry holding the token (its unigram state);
           // the explicit arcs (order >= 1) win the maximum
+          uint64_t fm = __ballot(kGroups ? (alive && grp == gi && lown) : inch);
+          while (fm != 0ull) {  // uniform
+            const int jr = static_cast<int>(__builtin_ctzll(fm));
+            fm &= fm - 1ull;
+            const uint32_t rf = rdlane(static_cast<uint32_t>(kGroups ? lrow_g : row), jr);
+            float bo[NLA];
 #pragma unroll
-          for (int h = 0; h < SPL; ++h) {
-            uint64_t fm = __ballot(kGroups ? (alive[h] && grp[h] == gi && lown[h]) : inch[h]);
-            while (fm != 0ull) {  // uniform
-              const int jr = static_cast<int>(__builtin_ctzll(fm));
-              fm &= fm - 1ull;
-              const uint32_t rf = rdlane(static_cast<uint32_t>(kGroups ? lrow_g[h] : row[h]), jr);
-              float bo[NLA];
+            for (int l = 0; l < NL; ++l) bo[l] = rdlane(lvbo[l], jr);
 #pragma unroll
-              for (int l = 0; l < NL; ++l) bo[l] = rdlane(lvbo[h][l], jr);
+            for (int jj = 0; jj < LPT; ++jj) {
+              if (tid + jj * kThreads < V) {
+                float v = rP1[jj];
 #pragma unroll
-              for (int jj = 0; jj < LPT; ++jj) {
-                if (tid + jj * kThreads < V) {
-                  float v = rP1[jj];
-#pragma unroll
-                  for (int l = 0; l < NL; ++l) v = v + bo[l];
-                  const float av = alpha * v;
-                  atomicMax(reinterpret_cast<unsigned long long*>(&lmrow[rf * static_cast<uint32_t>(V) + rcc[jj]]),
-                            (static_cast<unsigned long long>(genhi | rcc[jj]) << 32) | __float_as_uint(av));
-                }
+                for (int l = 0; l < NL; ++l) v = v + bo[l];
+                const float av = alpha * v;
+                atomicMax(reinterpret_cast<unsigned long long*>(&lmrow[rf * static_cast<uint32_t>(V) + rcc[jj]]),
+                          (static_cast<unsigned long long>(genhi | rcc[jj]) << 32) | __float_as_uint(av));
               }
             }
           }
@@ -823,7 +677,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
             const uint32_t rf = rdlane(static_cast<uint32_t>(rowof), jr);
             float bo[NLA];
 #pragma unroll
-            for (int l = 0; l < NL; ++l) bo[l] = rdlane(lvbo[0][l], jr);
+            for (int l = 0; l < NL; ++l) bo[l] = rdlane(lvbo[l], jr);
 #pragma unroll
             for (int jj = 0; jj < LPT; ++jj) {
               if (tid + jj * kThreads < V) {
@@ -894,26 +748,23 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
         // same scheme, one segment per beam (its merged continuation list)
         int S = 0;
         uint32_t bg_cnt = 0u, bg_base = 0u, bg_row = 0u;
-#pragma unroll
-        for (int h = 0; h < SPL; ++h) {
-          // the beams that fill a boosting row (the list's first with fill groups)
-          const bool bsel = kGroups ? (alive[h] && grp[h] == gi && bown[h]) : inch[h];
-          const uint32_t nb = bsel ? btc[h] : 0u;
-          const uint64_t m = __ballot(nb != 0u);
-          const int nl = __popcll(m);
-          if (nl > 0) {  // wave-uniform
-            const int dst = (nb != 0u) ? S + __popcll(m & lmlt) : ((S + nl) & 63);
-            const int addr = dst << 2;
-            const uint32_t r_cnt = static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, static_cast<int>(nb)));
-            const uint32_t r_base = static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, static_cast<int>(btb[h])));
-            const uint32_t r_row = static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, kGroups ? brow_g[h] : row[h]));
-            if (lane >= S && lane < S + nl) {
-              bg_cnt = r_cnt;
-              bg_base = r_base;
-              bg_row = r_row;
-            }
-            S += nl;
+        // the beams that fill a boosting row (the list's first with fill groups)
+        const bool bsel = kGroups ? (alive && grp == gi && bown) : inch;
+        const uint32_t nb = bsel ? btc : 0u;
+        const uint64_t m = __ballot(nb != 0u);
+        const int nl = __popcll(m);
+        if (nl > 0) {  // wave-uniform
+          const int dst = (nb != 0u) ? S + __popcll(m & lmlt) : ((S + nl) & 63);
+          const int addr = dst << 2;
+          const uint32_t r_cnt = static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, static_cast<int>(nb)));
+          const uint32_t r_base = static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, static_cast<int>(btb)));
+          const uint32_t r_row = static_cast<uint32_t>(__builtin_amdgcn_ds_permute(addr, kGroups ? brow_g : row));
+          if (lane >= S && lane < S + nl) {
+            bg_cnt = r_cnt;
+            bg_base = r_base;
+            bg_row = r_row;
           }
+          S += nl;
         }
         if (S > 0) {  // wave-uniform
           const int btl = static_cast<int>((bg_cnt + 63u) >> 6);
@@ -1205,7 +1056,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       };
       if (ch == 0 && wave == 0 && lane < K) {
         // blank candidates of every slot into the reserved region
-        const float x = sc[0] + rBlank;
+        const float x = sc + rBlank;
         const bool ok = x > kNegInf;  // (a NaN is no candidate)
         s_res[mpar][j] = make_uint4(__float_as_uint(ok ? x : kNegInf),
                                     ok ? static_cast<uint32_t>(j * W + V) : 0xFFFFFFFFu, 0u, 0u);
@@ -1216,10 +1067,9 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       }
       // Maxima of disjoint candidate groups are distinct candidates, so the
       // K-th largest of at least K group maxima bounds the K-th best candidate
-      // from below.  One slot per lane: groups (row, wave) of this chunk, and
-      // for K <= 8 also (row, half of the waves) and the waves; the groups of
-      // earlier chunks of the frame still count.  Two slots per lane: 128
-      // groups of 4 lanes.
+      // from below: groups (row, wave) of this chunk, and for K <= 8 also (row,
+      // half of the waves) and the waves; the groups of earlier chunks of the
+      // frame still count.
       {
         // The wave maxima of 8 row groups (row i, and i + 8 when a chunk has
         // 16 rows): a transposed reduction halves the groups a lane carries
@@ -1257,7 +1107,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       // score also bounds the K-th best from below (registers only: small
       // beams take it before the barrier)
       const auto blank_bound = [&]() __attribute__((always_inline)) {
-        float tb = (lane < K) ? no_nan(sc[0] + rBlank) : __builtin_huge_valf();
+        float tb = (lane < K) ? no_nan(sc + rBlank) : __builtin_huge_valf();
         tb = fmin_sel(tb, xor_lane(tb, 1, lane));
         tb = fmin_sel(tb, xor_lane(tb, 2, lane));
         tb = fmin_sel(tb, xor_lane(tb, 4, lane));
@@ -1374,10 +1224,8 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       // The best K go to region Q in rank order; after the last chunk the
       // winners' successor records go to s_rec[rcur ^ 1] instead.  Before
       // the last chunk the rank runs only when the pool is more than half
-      // full (a quarter with two slots per lane, whose block rank costs the
-      // square of the pool; an earlier rank also tightens the bound) or
-      // overflowed: otherwise the survivors stay in the pool for the next
-      // chunk (with large beams most chunks skip it).
+      // full or overflowed: otherwise the survivors stay in the pool for the
+      // next chunk.
       const bool last_chunk = ch + 1 == nch;
       const int npool = s_nbuf;
       if (SKIP && !last_chunk && !s_overflow && npool <= kCap / 2) {  // uniform
@@ -1473,8 +1321,8 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
             }
             if (last_chunk) {
               __syncthreads();  // region Q complete
-              // rank tid (waves 0 .. SPL-1): the chain-header loads of all
-              // winners are in flight together
+              // rank tid (wave 0): the chain-header loads of all winners are
+              // in flight together
               const bool act = wave == 0 && tid < min(K, nfin);
               uint4 e = make_uint4(__float_as_uint(kNegInf), 0xFFFFFFFFu, 0u, 0u);
               if (act) e = s_res[Q][tid];
@@ -1596,7 +1444,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
           }
           if (last_chunk) {
             __syncthreads();  // region Q complete
-            // rank tid (waves 0 .. SPL-1)
+            // rank tid (wave 0)
             const bool act = wave == 0 && tid < nk;
             uint4 e = make_uint4(__float_as_uint(kNegInf), 0xFFFFFFFFu, 0u, 0u);
             if (act) e = s_res[Q][tid];
@@ -1680,22 +1528,22 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       // (vmcnt counts stores and loads in issue order)
       if (wave == 1 && j < K) bpb[static_cast<size_t>(t) * K + j] = valid ? static_cast<int32_t>(rec[kRBp]) : -1;
       // new state
-      sc[0] = x;
-      last[0] = nlast;
-      len[0] = nlen;
-      alive[0] = nalive;
+      sc = x;
+      last = nlast;
+      len = nlen;
+      alive = nalive;
       int32_t acnt = 0;
 #pragma unroll
       for (int l = 0; l < NL; ++l) {
-        lvb[0][l] = nalive ? rec[kRLvb + l] : 0u;
-        lvc[0][l] = nalive ? rec[kRLvc + l] : 0u;
-        lvbo[0][l] = nalive ? __uint_as_float(rec[kRLvbo + l]) : 0.0f;
-        acnt += static_cast<int32_t>(lvc[0][l] & ~kExists);
+        lvb[l] = nalive ? rec[kRLvb + l] : 0u;
+        lvc[l] = nalive ? rec[kRLvc + l] : 0u;
+        lvbo[l] = nalive ? __uint_as_float(rec[kRLvbo + l]) : 0.0f;
+        acnt += static_cast<int32_t>(lvc[l] & ~kExists);
       }
       if (HAS_BT) {
-        btb[0] = nalive ? rec[kRBtb] : 0u;
-        btc[0] = nalive ? rec[kRBtc] : 0u;
-        btpot[0] = nalive ? static_cast<int32_t>(rec[kRBtp]) : 0;
+        btb = nalive ? rec[kRBtb] : 0u;
+        btc = nalive ? rec[kRBtc] : 0u;
+        btpot = nalive ? static_cast<int32_t>(rec[kRBtp]) : 0;
       }
       if (want_stats && wave == 0) {
         // chain work of the next frame (alive beams) and this frame's
@@ -1705,9 +1553,9 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
         if (counted) {
 #pragma unroll
           for (int l = 0; l < NL; ++l) {
-            if (lvc[0][l] & kExists) {
+            if (lvc[l] & kExists) {
               s_ls += 1u;
-              s_la += lvc[0][l] & ~kExists;
+              s_la += lvc[l] & ~kExists;
             }
           }
           if (HAS_BT) {
@@ -1782,21 +1630,15 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
           mm = __ballot(miss);
         }
       }
-      if constexpr (kGroups) {
-        const bool nal[1] = {nalive};
-        const int32_t ac[1] = {acnt};
-        const uint32_t lk[1] = {(HAS_LM && NL > 0 && nalive) ? rec[kRLms] : 0u};  // a unigram LM fills no row
-        int lpa[1] = {lp};
-        plan_groups(nal, ac, lk, lpa);
-        lp = lpa[0];
-      }
+      if constexpr (kGroups)  // (a unigram LM fills no row)
+        plan_groups(nalive, acnt, (HAS_LM && NL > 0 && nalive) ? rec[kRLms] : 0u, lp);
       CTCBEAM_PHASE_MARK(13);
-      if (wave == 2 && nalive) put_row(lp, 0);
+      if (wave == 2 && nalive) put_row(lp);
       // chunk plan: live slots in slot order, at most kcmax beams and
       // kLmStage staged arcs per chunk (cached rows stage nothing)
       if constexpr (CACHE) {
         nch = na > 0 ? 1 : 0;  // K <= KCR = kcmax, nothing staged
-        cid[0] = 0;
+        cid = 0;
       } else if constexpr (kGroups) {
         // planned above
       } else {
@@ -1804,10 +1646,10 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       const int tota = rdlane(ia, 63);
       if (na <= kcmax && tota <= kLmStage) {
         nch = na > 0 ? 1 : 0;
-        cid[0] = 0;
+        cid = 0;
       } else {
         nch = 0;
-        cid[0] = -1;
+        cid = -1;
         int start = 0;
         while (start < na) {
           const uint64_t sm = __ballot(nalive && lp == start);
@@ -1819,7 +1661,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
             cnt = 1;  // a single chain above the staging limit (the builders prevent it)
             status |= 4u;
           }
-          if (nalive && lp >= start && lp < start + cnt) cid[0] = nch;
+          if (nalive && lp >= start && lp < start + cnt) cid = nch;
           ++nch;
           start += cnt;
         }
@@ -1840,7 +1682,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   const bool nbest = p.nbest_scores != nullptr;
   float fin = kNegInf;  // wave 0: final score of the slot, -inf for a dead one
   if (wave == 0) {
-    float s = sc[0];
+    float s = sc;
     if (HAS_LM && j < K && s != kNegInf) {
       // ln P(</s> | state) through the backoff chain; </s> is the last arc of
       // a state's sorted arcs when present
@@ -1849,9 +1691,9 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
       float fv = 0.0f;
 #pragma unroll
       for (int l = NL - 1; l >= 0; --l) {
-        const uint32_t n = lvc[0][l] & ~kExists;
+        const uint32_t n = lvc[l] & ~kExists;
         if (found < 0 && n > 0) {
-          const LmArc a = p.lm_arcs[lvb[0][l] + n - 1];
+          const LmArc a = p.lm_arcs[lvb[l] + n - 1];
           if (a.token == static_cast<uint32_t>(V)) {
             found = l;
             fv = a.logp;
@@ -1862,17 +1704,17 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
         v = fv;
 #pragma unroll
         for (int l = 0; l < NL; ++l)
-          if (l > found) v = v + lvbo[0][l];
+          if (l > found) v = v + lvbo[l];
       } else {
 #pragma unroll
-        for (int l = 0; l < NL; ++l) v = v + lvbo[0][l];
+        for (int l = 0; l < NL; ++l) v = v + lvbo[l];
       }
       const float av = alpha * v;
       s = s + av;
     }
     if (HAS_BT && (p.flags & kFlagBoostRollback) && j < K && s != kNegInf) {
       // the pending boosting of an unfinished phrase is taken back
-      const float wb = boost_w * static_cast<float>(-btpot[0]);
+      const float wb = boost_w * static_cast<float>(-btpot);
       s = s + wb;
     }
     // rank of each slot: final score descending, lowest slot on ties (a NaN
@@ -1887,8 +1729,8 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
     const uint64_t top = __ballot(j < K && rank == 0);
     const int bj = static_cast<int>(__builtin_ctzll(top));  // K >= 1: some slot has rank 0
     const float bs = rdlane(sj, bj);
-    const int blen = rdlane(len[0], bj);
-    const int nlen = (j < K && sj != kNegInf) ? len[0] : 0;
+    const int blen = rdlane(len, bj);
+    const int nlen = (j < K && sj != kNegInf) ? len : 0;
     if (nbest && j < K) {
       p.nbest_scores[static_cast<size_t>(b) * K + rank] = sj;
       p.nbest_lengths[static_cast<size_t>(b) * K + rank] = nlen;
@@ -1943,7 +1785,7 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
     int pos = 0;
     if (walker) {
       orow = nbest ? nbt + static_cast<size_t>(s_row[KMX + j]) * T : ot;
-      pos = nbest ? len[0] : nout;
+      pos = nbest ? len : nout;
     }
     for (int hi = L; hi > 0;) {
       const int lo = hi > tile_frames ? hi - tile_frames : 0;
@@ -2015,9 +1857,10 @@ template <int LPT, int NLEV, bool REP>
 hipError_t launch_nlev(const KernelParams& p, hipStream_t s) {
   // beams of more than one chunk (16 / LPT rows) skip ranks
   if constexpr (multi_chunk(LPT, NLEV, true) || multi_chunk(LPT, NLEV, false)) {
+    if (p.K > 16) return hipErrorInvalidValue;
     if (p.K > 16 / LPT) return launch_skip<LPT, NLEV, true, REP>(p, s);
   }
-  if (p.K > 16 / LPT) return hipErrorInvalidValue;
+  if (p.K > 16 / LPT) return hipErrorInvalidValue;  // (class_eligible takes them)
   return launch_skip<LPT, NLEV, false, REP>(p, s);
 }
 
