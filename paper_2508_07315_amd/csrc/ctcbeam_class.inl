@@ -1363,7 +1363,9 @@ __global__ void __launch_bounds__(kCT) class_kernel(KernelParams p) {
           if (SPL > 1 && h > 0) low |= __ballot(klo[0] == l0 && khi[0] == h0);
           if (low != 0ull) mine[h] |= (1ull << i) & live;
         }
-        if (lane == 0) s_dup[wave][h] = mine[h];
+        // (per-lane address: a uniform one, s_dup[wave] in lane 0, lengthens
+        // other live ranges and costs 3 % at K = 94 without models)
+        if (lane < 1) s_dup[wave + lane][h] = mine[h];
       }
       __syncthreads();
 #pragma unroll
