@@ -1825,13 +1825,6 @@ __global__ void __launch_bounds__(kThreads) decode_kernel(KernelParams p) {
   }
 }
 
-// Whether class_eligible leaves beams of several chunks to this decoder at LPT
-// labels per lane, for an LM of NLEV levels (-1: none).
-constexpr bool multi_chunk(int LPT, int NLEV, bool boosting) {
-  if (LPT == 8) return NLEV >= 0 || boosting;
-  return LPT == 4 && boosting && (NLEV == 2 || NLEV == 3);
-}
-
 template <int LPT, int NLEV, bool SKIP, bool REP>
 hipError_t launch_skip(const KernelParams& p, hipStream_t s) {
   dim3 grid(p.B), block(kThreads);

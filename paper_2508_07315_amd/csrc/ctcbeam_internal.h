@@ -212,6 +212,14 @@ inline bool class_eligible(const KernelParams& p) {
   return p.V <= 2560;
 }
 
+// The general decoder's forms for beams of several chunks, of which a chunk
+// takes 16 / lpt: whether class_eligible leaves it some at lpt labels per lane,
+// for an LM of nlev levels (-1: none).
+constexpr bool multi_chunk(int lpt, int nlev, bool boosting) {
+  if (lpt == 8) return nlev >= 0 || boosting;
+  return lpt == 4 && boosting && (nlev == 2 || nlev == 3);
+}
+
 inline hipError_t launch_decode(const KernelParams& p, hipStream_t stream) {
   if (p.B == 0) return hipSuccess;
   if (small_beam_eligible(p)) return launch_small(p, stream);
