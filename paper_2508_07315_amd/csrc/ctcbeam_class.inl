@@ -54,13 +54,13 @@
 //
 // Measured against the general decoder, which scored V labels per beam (400
 // frames, 1024 tokens; ms a launch): 32 utterances with a 6-gram and 1000
-// phrases, 10.7 -> 8.2 at K = 16 and 91 -> 38.8 at K = 128; 64 with a 3-gram
-// and 5000 phrases at K = 64, 26.7 -> 14.0.  With 45 tokens, a 3-gram and 50
-// phrases (24 utterances of 600 frames, K = 32) 16.8 -> 6.2.  A frame takes
-// 48 k cycles at K = 16, 74 k at K = 64 and 209 k at K = 128 (6-gram); at
-// K = 64 the fills take 21 k of it, naming classes and rows 13 k, the
-// expansion with its barrier 15 k, the scoring 8 k: dependent LDS and memory
-// round trips, not bandwidth.
+// phrases, 11.3 -> 8.5 at K = 16 and 98 -> 38.6 at K = 128; 64 with a 3-gram
+// and 5000 phrases at K = 64, 25.5 -> 13.0.  With 45 tokens, a 3-gram and 50
+// phrases (24 utterances of 600 frames, K = 32) 16.8 -> 6.1.  On those inputs a
+// frame takes 46 k cycles at K = 16, 74 k at K = 64, 200 k at K = 128 and 25 k
+// over 45 tokens (profiling build); at K = 64 the fills take 21 k of it, naming
+// classes and rows 15 k, the expansion with its barrier 16 k, the scoring 9 k:
+// dependent LDS and memory round trips, not bandwidth.
 // Eight waves, two a SIMD, hide those better than four (K = 64: 15.3 against
 // 18.4 ms); passes of 16 classes cost fewer phases than passes of 8 (K = 16:
 // 9.5 -> 8.9 ms with the arcs dealt out); bounding a class by its best beam

@@ -34,16 +34,18 @@
 // (score, flat index), and the places at the K-th best score go to the lowest
 // flat indices of all candidates with that score.
 //
-// The chain of wave 0 bounds it, about 2.2 k cycles a frame: a wave alone on its
-// SIMD issues a dependent instruction every 7 to 8 cycles and waits about 130
-// for LDS.  So the rank takes the signs of differences instead of compares and
-// carries, a winner brings its new transcript hash with it (formed in every
-// entry's lane while the scores settle in LDS) instead of reading its parent's
-// afterwards, and the next frame's list entry is read a frame ahead (32
-// utterances of 400 frames, V = 1024, K = 8: 0.68 -> 0.43 ms; the form before
-// the lists, with every label scored for every beam behind three barriers a
-// frame, took 1.48).  The lists themselves cost nothing that shows.  One
-// utterance of 50 frames, V = 32, K = 4: 0.11 -> 0.042 ms.
+// The chain of wave 0 bounds it, about 2.5 k cycles a frame (423 us for 400
+// frames): a wave alone on its SIMD issues a dependent instruction every 7 to 8
+// cycles and waits about 130 for LDS.  So the rank takes the signs of
+// differences instead of compares and carries, a winner brings its new
+// transcript hash with it (formed in every entry's lane while the scores settle
+// in LDS) instead of reading its parent's afterwards, and the next frame's list
+// entry is read a frame ahead (32 utterances of 400 frames, V = 1024, K = 8:
+// 0.68 -> 0.43 ms; the form before the lists, with every label scored for every
+// beam behind three barriers a frame, took 1.48).  The lists themselves cost
+// nothing that shows.  One utterance of 50 frames, V = 32, K = 4: 0.114 ->
+// 0.038 ms with the code warm, 0.170 -> 0.089 ms for a first call on new inputs,
+// which is mostly the launch and cold code.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
