@@ -1,8 +1,8 @@
 """GPU parity at paper scale: a subword 6-gram LM with 11 M n-grams (the paper
 decodes with KenLM 6-grams, Sec. IV-A), 1000 boosted phrases, theta = 12
 (Sec. IV-D), beams 4-64 (Fig. "beam_size_vs_wer"; K = 8 fills all rows of a
-chunk, K = 4 and 8 with the fold kept in the rows of one chunk, 16 and 64
-across chunks), through the C ABI against
+chunk, K = 4 and 8 with the fold kept in the rows of one chunk of the general
+decoder, 16 and 64 on the class decoder), through the C ABI against
 the CPU oracle.  Tokens bit-exact, scores within 1e-4.
 """
 import math

@@ -5,13 +5,14 @@ fl(w*BT) terms again) against the CPU oracle with the same rule.
 Bar: tokens bit-exact, scores within 1e-4.
 
 * the workloads at reduced sizes, 1-best, N-best and greedy, theta = inf and
-  12: row-cached LM rows (K = 8, 3-gram), boosting (4-gram + phrases, K = 16)
-  and chunked beams with rank skipping (K = 64);
+  12: the general decoder (K = 8, 3-gram) and the class decoder (4-gram +
+  phrases, K = 16, and K = 64);
 * the path without the row cache, and two slots per lane (K = 128);
 * exhaustive inputs (K >= (V+1)^T), N-best;
 * constant rows with boosting: every candidate ties within its boosting
-  class, so the survivor pool overflows and the exact fallback carries the
-  terms of its winners.
+  class, so the pool overflows and the general decoder's exact fallback (K = 8)
+  or the class decoder's raised bound (K = 64) carries the terms of its
+  winners.
 """
 import math
 
