@@ -344,8 +344,7 @@ __global__ void __launch_bounds__(64 * NW) greedy_kernel(KernelParams p) {
     // zero) are needed only when a label of this wave can beat the blank,
     // which has the largest index and wins only when strictly better
     const float g = wave_max(xb);
-    const float sb = s + dbl;
-    const float xblank = (sb == sb) ? sb : kNegInf;  // (a NaN is no candidate)
+    const float xblank = fmaxf(s + dbl, kNegInf);  // (a NaN is no candidate)
     const bool need = !(xblank > g) && g != kNegInf;  // uniform per wave
     int cw = V;
     float xw = kNegInf;
